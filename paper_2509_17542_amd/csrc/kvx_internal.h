@@ -114,6 +114,12 @@ struct KArgs {
     int32_t src_block_size;
     FastDiv div_sbs;
     int32_t sbt_uniform;              // every part lies in one source page
+    // flat launches: the rows of a plane's pages packed into workgroups
+    int32_t flat;                     // units are planes x groups x segments
+    uint32_t groups;                  // workgroups per plane and segment
+    uint32_t row_lanes;               // lanes per row: cpr, or the power of two above it
+    uint32_t page_rows;               // rows of a page in its widest segment
+    FastDiv div_groups, div_row_lanes, div_page_rows;
 };
 
 // Launch one conversion over a.units work units; returns a hipError_t value.

@@ -35,6 +35,16 @@
 // non-temporal: every row is read once and the destination is not read again
 // by this launch.
 //
+// Flat launches.  The units above give every page whole workgroups, which is
+// what makes the page's addresses scalar; where that leaves many lanes idle
+// (one-token pages, one head per decode rank, rows whose 16-byte chunks are not
+// a power of two), a launch is flat instead: the rows of consecutive pages of a
+// plane and segment are numbered through and packed into the workgroups, and
+// each lane looks its own page up.  16-bit rows whose chunks fill at most 3/4
+// of a power of two are packed chunk by chunk, so that no lane is idle but
+// those past a request's last token.  The per-lane lookups cost 4-15% where
+// the lanes are full either way; the planner's rule has both sides measured.
+//
 // The path is a gather/scatter stream with no reuse and no contraction: the
 // 16-bit conversions are bound by HBM bandwidth, the 8-bit ones (e4m3fn,
 // e5m2, per-row scales) by the vector ALUs and HBM together.  There is no
@@ -194,9 +204,8 @@ struct SrcFmt {
 // General path: one lane's 2*NW source elements (NW 32-bit words) -> 2*NW
 // 8-bit codes, every case of the definition (NaN elements, zero rows, scales
 // too small or too large for the two-step divide), element by element in
-// software.  The row maximum is reduced over the lanes-per-row group (2^lg
-// lanes, consecutive, so xor shuffles stay inside the group); every lane of the
-// wave must execute the reduction.
+// software.  The row maximum is reduced over the row's lanes, all of which
+// must execute the reduction.
 template <int CONV, int NW>
 __device__ __forceinline__ void fp8_codes_general(const uint32_t (&w)[NW], int lg,
                                                   float& scale_out, uint32_t (&out)[NW / 2])
@@ -484,17 +493,17 @@ __device__ __forceinline__ uint4 load_stream(const char* p)
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// Read one dword at the start of the destination page of the unit
-// kPrefetchPages pages after `unit` (same plane-major order), so that its
-// address translation is cached before that page's workgroups store to it.
-// The value is discarded; ids outside the pool are ignored.
-__device__ __forceinline__ void warm_translation(const KArgs& a, uint32_t unit)
+// Read one dword at the start of the destination page kPrefetchPages pages
+// after page `page_unit` (plane-major, as the units), so that its address
+// translation is cached before that page's workgroups store to it.  The value
+// is discarded; ids outside the pool are ignored.
+__device__ __forceinline__ void warm_translation(const KArgs& a, uint32_t page_unit)
 {
-    const uint32_t fu = unit + uint32_t(kPrefetchPages) * a.parts * a.num_segs;
-    if (fu >= a.units) return;
-    const uint32_t page_unit = fdiv(fdiv(fu, a.div_parts), a.div_segs);
-    const uint32_t plane = fdiv(page_unit, a.div_items) + a.dst_plane0;  // cache plane
-    const Item it = a.items[page_unit - (plane - a.dst_plane0) * a.num_items];
+    const uint32_t fp = page_unit + uint32_t(kPrefetchPages);
+    const uint32_t fplane = fdiv(fp, a.div_items);
+    if (fplane >= a.planes) return;
+    const uint32_t plane = fplane + a.dst_plane0;  // cache plane
+    const Item it = a.items[fp - fplane * a.num_items];
     const int32_t b = a.bt[int64_t(it.req) * a.bt_stride + it.blk];
     if (b < 0 || b >= a.num_blocks) return;
     const volatile uint32_t* q = reinterpret_cast<const volatile uint32_t*>(
@@ -503,7 +512,7 @@ __device__ __forceinline__ void warm_translation(const KArgs& a, uint32_t unit)
     (void)*q;
 }
 
-template <int MODE, int CONV, int ORDER>
+template <int MODE, int CONV, int ORDER, bool FLAT>
 __device__ __forceinline__ void convert_part(const KArgs& a)
 {
     constexpr bool kFp8 = CONV == kBf16E4m3 || CONV == kF16E4m3 ||    // writes 8-bit codes
@@ -539,21 +548,45 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
     // and 8-bit paths measure 2-4% faster with the row load inside the
     // branch, and the pack from paged sources the same either way.
     constexpr bool kEarly =
-        (ORDER == KVX_PAGED && MODE != kPack) ||
+        FLAT || (ORDER == KVX_PAGED && MODE != kPack) ||
         (ORDER == KVX_THD && (CONV == kCopy16 || CONV == kF16Bf16 || CONV == kBf16F16));
 
     // XCD-contiguous unit of this workgroup -> (plane, page, segment, part)
     const uint32_t unit = (blockIdx.x % kXcds) * a.units_per_xcd + blockIdx.x / kXcds;
     if (unit >= a.units) return;  // the grid is rounded up to a multiple of kXcds
-    const uint32_t q1 = fdiv(unit, a.div_parts);
-    const uint32_t part = unit - q1 * a.parts;
-    const uint32_t q2 = fdiv(q1, a.div_segs);
-    const uint32_t sg = q1 - q2 * a.num_segs;
-    const uint32_t plane = fdiv(q2, a.div_items);           // layer * 2 + k/v
-    const uint32_t item = q2 - plane * a.num_items;
-    if (plane >= a.planes || item >= a.num_items || sg >= a.num_segs || part >= a.parts) return;
+    uint32_t plane, sg, part = 0;  // plane: layer * 2 + k/v
+    uint32_t page_unit;            // plane * pages + page
+    Item it;
+    int sub, r;                    // 16-byte chunk within the row, row within the segment
+    bool live = true;              // the lane has a place in a page
+    if constexpr (FLAT) {
+        const uint32_t q1 = fdiv(unit, a.div_segs);
+        sg = unit - q1 * a.num_segs;
+        plane = fdiv(q1, a.div_groups);
+        const uint32_t group = q1 - plane * a.groups;
+        if (plane >= a.planes) return;
+        // slot -> row of the plane and segment (page x rows of a page + row of the page)
+        const uint32_t slot = group * kThreads + threadIdx.x;
+        const uint32_t row = fdiv(slot, a.div_row_lanes);
+        sub = int(slot - row * a.row_lanes);
+        const uint32_t item = fdiv(row, a.div_page_rows);
+        r = int(row - item * a.page_rows);
+        live = item < a.num_items;
+        page_unit = plane * a.num_items + item;
+        it = a.items[live ? item : 0u];
+    } else {
+        const uint32_t q1 = fdiv(unit, a.div_parts);
+        part = unit - q1 * a.parts;
+        page_unit = fdiv(q1, a.div_segs);
+        sg = q1 - page_unit * a.num_segs;
+        plane = fdiv(page_unit, a.div_items);
+        const uint32_t item = page_unit - plane * a.num_items;
+        if (plane >= a.planes || item >= a.num_items || sg >= a.num_segs || part >= a.parts) return;
+        it = a.items[item];
+        sub = threadIdx.x & ((1 << a.lg_lpr) - 1);
+        r = int(part) * (kThreads >> a.lg_lpr) + (threadIdx.x >> a.lg_lpr);
+    }
     const Segment seg = a.seg[sg];
-    const Item it = a.items[item];
     const int T = it.tokens;
     const int t0 = it.blk * a.block_size;
     const int seg_rows = min(a.block_size, T - t0) * seg.n;
@@ -566,7 +599,7 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
     // workgroup, looked up once (the part's first token must exist).
     int32_t sb_u = -1;
     uint32_t q_u = 0;
-    if constexpr (ORDER == KVX_PAGED && MODE != kUnpack) {
+    if constexpr (ORDER == KVX_PAGED && MODE != kUnpack && !FLAT) {
         if (a.sbt_uniform) {
             const uint32_t tf = uint32_t(t0) + fdiv(part * uint32_t(kThreads >> lg), seg.div_n);
             if (tf < uint32_t(T)) {
@@ -576,8 +609,6 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
         }
     }
 
-    const int sub = threadIdx.x & ((1 << lg) - 1);          // 16-byte chunk within the row
-    const int r = int(part) * (kThreads >> lg) + (threadIdx.x >> lg);  // row within the segment
     int s, ii;  // token within the page, head within the segment
     bool ok;
     if constexpr (ORDER == KVX_HTD && MODE != kUnpack) {
@@ -585,11 +616,11 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
         // head, contiguous in a [head][token][dim] source
         ii = int(fdiv(uint32_t(r), a.div_bs));
         s = r - ii * a.block_size;
-        ok = sub < a.cpr && ii < seg.n && s < seg_rows / seg.n;
+        ok = live && sub < a.cpr && ii < seg.n && s < min(a.block_size, T - t0);
     } else {
         s = int(fdiv(uint32_t(r), seg.div_n));
         ii = r - s * seg.n;
-        ok = sub < a.cpr && r < seg_rows;
+        ok = live && sub < a.cpr && r < seg_rows;
     }
     const int row = s * a.hd + seg.i0 + ii;                 // row within the page
 
@@ -617,7 +648,7 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
             const uint32_t t = uint32_t(t0 + s);
             int32_t sb = sb_u;
             uint32_t q = q_u;
-            if (!a.sbt_uniform && ok) {
+            if ((FLAT || !a.sbt_uniform) && ok) {
                 q = fdiv(t, a.div_sbs);
                 sb = a.sbt[int64_t(it.req) * a.sbt_stride + q];
             }
@@ -679,8 +710,13 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
         if constexpr (kScales)
             sbase = reinterpret_cast<float*>(static_cast<char*>(a.dst) + it.wire_scale) + row0;
     } else {
-        if (part == 0 && sg == 0 && threadIdx.x == 0) warm_translation(a, unit);
-        if (b < 0 || b >= a.num_blocks) return;  // not a page of the pool: nothing written
+        const bool page = b >= 0 && b < a.num_blocks;  // else no page of the pool: nothing written
+        if constexpr (FLAT) {
+            ok = ok && page;
+        } else {
+            if (part == 0 && sg == 0 && threadIdx.x == 0) warm_translation(a, page_unit);
+            if (!page) return;
+        }
         const int64_t page_rows = int64_t(b) * a.block_size * a.hd;
         const uint32_t cplane = plane + a.dst_plane0;  // the cache's own layer
         dbase = static_cast<char*>(a.dst) + cplane * a.plane_bytes + page_rows * a.row_dst_bytes;
@@ -713,10 +749,10 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
         if constexpr (kHalves)
             __builtin_nontemporal_store(__builtin_bit_cast(v4u, out2),
                                         reinterpret_cast<v4u*>(drow + (sub + a.cpr) * 16));
-        if constexpr (kScales && !kFp8)  // the 8-bit unpack: the scale it loaded
+        if constexpr (kScales && (FLAT || !kFp8))  // the 8-bit unpack: the scale it loaded
             if (sub == 0) __builtin_nontemporal_store(sc, sbase + row);
     }
-    if constexpr (kFp8) {
+    if constexpr (kFp8 && !FLAT) {
         // The quantising launches' 4-byte row scales go out through LDS: lane
         // 0 of each row leaves its scale and destination slot there, and after
         // the barrier the first lanes of wave 0 store them all, so a
@@ -742,22 +778,22 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
 }
 
 // One kernel name per operation, so traces tell them apart.
-template <int CONV, int ORDER>
+template <int CONV, int ORDER, bool FLAT>
 __global__ void __launch_bounds__(kThreads) kvx_pack_kernel(const KArgs a)
 {
-    convert_part<kPack, CONV, ORDER>(a);
+    convert_part<kPack, CONV, ORDER, FLAT>(a);
 }
 
-template <int CONV, int ORDER>
+template <int CONV, int ORDER, bool FLAT>
 __global__ void __launch_bounds__(kThreads) kvx_unpack_kernel(const KArgs a)
 {
-    convert_part<kUnpack, CONV, ORDER>(a);
+    convert_part<kUnpack, CONV, ORDER, FLAT>(a);
 }
 
-template <int CONV, int ORDER>
+template <int CONV, int ORDER, bool FLAT>
 __global__ void __launch_bounds__(kThreads) kvx_repack_kernel(const KArgs a)
 {
-    convert_part<kRepack, CONV, ORDER>(a);
+    convert_part<kRepack, CONV, ORDER, FLAT>(a);
 }
 
 template <int MODE, int CONV, int ORDER>
@@ -765,11 +801,14 @@ int go(const KArgs& a, void* stream)
 {
     const void* fn;
     if constexpr (MODE == kPack)
-        fn = reinterpret_cast<const void*>(&kvx_pack_kernel<CONV, ORDER>);
+        fn = a.flat ? reinterpret_cast<const void*>(&kvx_pack_kernel<CONV, ORDER, true>)
+                    : reinterpret_cast<const void*>(&kvx_pack_kernel<CONV, ORDER, false>);
     else if constexpr (MODE == kUnpack)
-        fn = reinterpret_cast<const void*>(&kvx_unpack_kernel<CONV, ORDER>);
+        fn = a.flat ? reinterpret_cast<const void*>(&kvx_unpack_kernel<CONV, ORDER, true>)
+                    : reinterpret_cast<const void*>(&kvx_unpack_kernel<CONV, ORDER, false>);
     else
-        fn = reinterpret_cast<const void*>(&kvx_repack_kernel<CONV, ORDER>);
+        fn = a.flat ? reinterpret_cast<const void*>(&kvx_repack_kernel<CONV, ORDER, true>)
+                    : reinterpret_cast<const void*>(&kvx_repack_kernel<CONV, ORDER, false>);
     void* args[] = {const_cast<KArgs*>(&a)};
     const unsigned grid = a.units_per_xcd * kXcds;
     return int(hipLaunchKernel(fn, dim3(grid), dim3(kThreads), args, 0,

@@ -494,7 +494,45 @@ void fill_args(const kvx_desc& d, const kvx::Shape& s, int mode, uint32_t num_it
         a.parts = uint32_t(s.parts);
         for (int k = 0; k < s.nsegs; ++k) a.seg[k] = s.segs[k];
     }
-    const int64_t units = int64_t(num_items) * a.planes * a.num_segs * a.parts;
+    // Flat launches (see the kernels).  Two shares of the page-aligned form's
+    // lanes decide: those that cover a row (cpr of 2^lg_lpr), and those that
+    // the rows of a page fill of its whole workgroups.
+    //  - Rows are packed chunk by chunk when they fill at most 3/4 of their
+    //    lanes.  14266 tokens, 32 layers, 8 heads bf16, 16-token pages:
+    //    head_dim 80 510 -> 422 us, 96 531 -> 507, but 112 591 -> 592.  A
+    //    paged source's repack, with a second lookup per lane, at 5/8 (80:
+    //    287 -> 254 us), its pack not (80: 246 -> 249, 96: 258 -> 289).  Not
+    //    from head-major sources (80: 575 -> 595) nor for dequantisation (80:
+    //    149 -> 185); quantising rows reduce over aligned lanes.
+    //  - Otherwise a launch is flat when a page's rows fill at most 3/4 of its
+    //    workgroups (8-bit types, bound by the vector ALUs as well: 5/8).
+    //    6-token pages of 4 heads x 128 (3/4) 414 -> 392 us, but 10-token
+    //    pages (5/6) 381 -> 390; one e4m3fn head, 20-token pages (5/8) 78 ->
+    //    73 us, 24-token ones (3/4) 69.5 -> 71.8, 16-token ones (1/2) 95 -> 80;
+    //    one-token pages of 2 heads x 80 616 -> 70 us.
+    // The flat units are never more than the others: a page's rows fit its
+    // whole workgroups.
+    int max_n = 0;
+    for (uint32_t k = 0; k < a.num_segs; ++k) max_n = std::max(max_n, a.seg[k].n);
+    a.page_rows = uint32_t(d.block_size) * uint32_t(max_n);
+    const int64_t lpr = int64_t(1) << s.lg_lpr;
+    int chunk_eighths = 6;  // of its lanes that a row packed chunk by chunk may fill
+    if (is_fp8(d.dst_dtype)) chunk_eighths = 0;
+    else if (mode != kvx::kUnpack && d.src_order == KVX_HTD) chunk_eighths = 0;
+    else if (mode != kvx::kUnpack && d.src_order == KVX_PAGED) chunk_eighths = mode == kvx::kPack ? 0 : 5;
+    const bool by_chunk = s.cpr * 8 <= lpr * chunk_eighths;
+    a.row_lanes = uint32_t(by_chunk ? s.cpr : lpr);
+    a.flat = by_chunk ||
+             int64_t(a.page_rows) * lpr * 8 <= int64_t(a.parts) * kvx::kThreads * (is_fp8(d.dst_dtype) ? 5 : 6);
+    int64_t units = int64_t(num_items) * a.planes * a.num_segs * a.parts;
+    if (a.flat) {
+        const int64_t lanes = int64_t(num_items) * a.page_rows * a.row_lanes;
+        a.groups = uint32_t((lanes + kvx::kThreads - 1) / kvx::kThreads);
+        units = int64_t(a.groups) * a.planes * a.num_segs;
+        a.div_groups = kvx::make_fastdiv(a.groups);
+        a.div_row_lanes = kvx::make_fastdiv(a.row_lanes);
+        a.div_page_rows = kvx::make_fastdiv(a.page_rows);
+    }
     a.units = uint32_t(units);
     a.units_per_xcd = uint32_t((units + kvx::kXcds - 1) / kvx::kXcds);
     a.div_parts = kvx::make_fastdiv(a.parts);
