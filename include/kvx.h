@@ -57,7 +57,8 @@
  *
  * Ownership: every buffer is caller-owned device memory; the library never
  * allocates or frees it.  A plan is library-owned: kvx_plan copies seq_lens
- * and allocates a small device table on the device current at that time.
+ * and, for more than one request with tokens, allocates a small device table
+ * on the device current at that time.
  *
  * Streams: kvx_pack / kvx_unpack / kvx_repack (and the _paged forms) only
  * enqueue work on the given hipStream_t (passed as void*, NULL = default

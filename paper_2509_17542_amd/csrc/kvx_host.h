@@ -50,6 +50,7 @@ struct kvx_plan_s {
     int64_t src_elems = 0;        // elements of a read source shard the launches may touch
     int64_t total_tokens = 0;
     int64_t elems_rows = 0;       // sum over requests of L*2*T*Hd
+    int32_t one_req = -1;         // the only request with pages, -1 if there are several (or none)
     int device = -1;
     void* dev_table = nullptr;    // device copy of items
     const kvx::Item* dev_items = nullptr;

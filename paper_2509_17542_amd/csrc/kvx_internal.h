@@ -13,7 +13,6 @@ constexpr int kMaxHeadsPerRank = 1024;  // Hd limit
 constexpr int kMaxReadShards = 64;      // head segments (and so source shards) of a decode rank
 constexpr int kMaxRowChunks = 64;       // 16-byte destination chunks per row (one wave)
 constexpr int kXcds = 8;                // MI355X: workgroups are dealt round-robin to 8 XCDs
-constexpr int kPrefetchPages = 32;      // pages ahead whose address translation a workgroup warms
 // work units of one launch; the 1-D grid is this rounded up to a multiple of
 // kXcds, and grid * kThreads stays below 2^32
 constexpr int64_t kMaxUnits = (int64_t(1) << 24) - kXcds;
@@ -68,61 +67,82 @@ enum Conv : int {
 };
 
 // A run of the decode rank's heads that comes from one source shard: decode
-// heads [i0, i0 + n) are heads [h0, h0 + n) of the shard at src[slot].
+// heads [i0, i0 + n) are heads [h0, h0 + n) of that shard.
 struct Segment {
-    int32_t slot;
+    const void* src;                  // the shard (launches; the unpack's transfer tensor)
+    int32_t slot;                     // the shard's place among the shards that are read
     int32_t h0;
     int32_t i0;
     int32_t n;
     FastDiv div_n;
 };
 
-// Kernel arguments (passed by value through the kernel-argument segment).
-struct KArgs {
-    const void* src[kMaxReadShards];  // the k-th shard the decode rank reads at src[k]
-    Segment seg[kMaxReadShards];      // pack/repack: the head segments; unpack: one, all heads
-    const void* wire_in;              // unpack source
-    void* dst;                        // pack: transfer tensor; else cache
-    float* dscale;                    // cache scales (unpack/repack into an 8-bit cache)
-    const Item* items;
-    const int32_t* bt;
-    int64_t num_blocks;
-    int64_t plane_bytes;              // cache bytes per (layer, k/v) plane
-    int64_t plane_scales;             // cache scales per plane
+// Kernel arguments (passed by value through the kernel-argument segment).  A
+// kernel reads the groups that its form needs whole, at its start, so that one
+// wait covers them all: Args, then Args2 (head-major, flat and 8-bit forms)
+// and ArgsPaged; a launch with one head segment does not read seg[].
+struct Args {
     uint32_t units;                   // work units: planes x pages x segments x parts
     uint32_t units_per_xcd;           // grid / kXcds
+    uint32_t num_segs;
     uint32_t num_items;               // logical pages per plane
     uint32_t planes;                  // 2 x converted layers
-    uint32_t src_plane0;              // 2 x source layer offset (pipeline stages)
-    uint32_t dst_plane0;              // 2 x cache layer offset
-    uint32_t num_segs;
-    uint32_t parts;                   // workgroup passes per (page, segment)
-    FastDiv div_parts, div_segs, div_items, div_bs;
+    uint32_t parts;                   // workgroup passes per (page, segment); flat launches:
+                                      // workgroups per plane and segment
+    FastDiv div_parts, div_segs, div_items;
+    const Item* items;
+    const int32_t* bt;
     int32_t bt_stride;
     int32_t block_size;
     int32_t hs;                       // heads per source shard
     int32_t hd;                       // heads per decode rank
     int32_t head_dim;
-    int32_t row_dst_bytes;            // pack: transfer-tensor row bytes; else cache row bytes
-    int32_t row_wire_bytes;           // transfer-tensor row bytes (the unpack's source rows)
     int32_t cpr;                      // 16-byte transfer-tensor chunks per row
     int32_t lg_lpr;                   // log2(lanes per row), lanes per row >= cpr
-    // paged sources: the prefill side's pages
+    int32_t row_dst_bytes;            // pack: transfer-tensor row bytes; else cache row bytes
+    uint32_t src_plane0;              // 2 x source layer offset (pipeline stages)
+    uint32_t dst_plane0;              // 2 x cache layer offset
+    void* dst;                        // pack: transfer tensor; else cache
+    int64_t num_blocks;
+    int64_t plane_bytes;              // cache bytes per (layer, k/v) plane
+    Segment seg0;                     // the only head segment where num_segs is 1
+    int32_t one_tokens;               // tokens of the only request with pages, 0: items[] holds them
+    int32_t row_wire_bytes;           // transfer-tensor row bytes (the unpack's source rows)
+    int64_t one_wire_scale;           // that request's Item::wire_scale (its other offsets are 0)
+    float* dscale;                    // cache scales (unpack/repack into an 8-bit cache)
+    int64_t plane_scales;             // cache scales per plane
+};
+
+struct Args2 {
+    FastDiv div_bs;
+    // flat launches: the rows of a plane's pages packed into workgroups
+    uint32_t row_lanes;               // lanes per row: cpr, or the power of two above it
+    uint32_t page_rows;               // rows of a page in its widest segment
+    FastDiv div_row_lanes, div_page_rows;
+};
+
+struct ArgsPaged {                    // paged sources: the prefill side's pages
     const int32_t* sbt;               // source block table [requests][sbt_stride]
     int64_t src_num_blocks;           // pages per plane of each shard's pool
     int32_t sbt_stride;
     int32_t src_block_size;
     FastDiv div_sbs;
     int32_t sbt_uniform;              // every part lies in one source page
-    // flat launches: the rows of a plane's pages packed into workgroups
-    int32_t flat;                     // units are planes x groups x segments
-    uint32_t groups;                  // workgroups per plane and segment
-    uint32_t row_lanes;               // lanes per row: cpr, or the power of two above it
-    uint32_t page_rows;               // rows of a page in its widest segment
-    FastDiv div_groups, div_row_lanes, div_page_rows;
+    int32_t pad;
 };
 
-// Launch one conversion over a.units work units; returns a hipError_t value.
+struct KArgs {
+    Args a;
+    Args2 b;
+    ArgsPaged p;
+    int32_t flat;                     // the launch is flat (read by the host)
+    int32_t pad;
+    Segment seg[kMaxReadShards];      // pack/repack: the head segments; unpack: one, all heads
+};
+static_assert(sizeof(Args) == 192 && sizeof(Args2) == 32 && sizeof(ArgsPaged) == 40,
+              "the kernels read the argument groups as whole dwords");
+
+// Launch one conversion over the arguments' work units; returns a hipError_t value.
 int launch(int mode, int conv, int order, const KArgs& a, void* stream);
 
 // The allocation-free repack keeps its work-item table in a static device

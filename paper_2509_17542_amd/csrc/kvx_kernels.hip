@@ -26,14 +26,8 @@
 // the source block table.  Rows of one token are contiguous in a source page,
 // as in a token-major source, so the unit and row order are the same.
 //
-// Destination pages of the paged cache are scattered over a pool of tens to
-// hundreds of GiB, so their first touch often waits for an address
-// translation.  The first workgroup of each page (part 0, segment 0) therefore
-// also reads one dword of the destination page kPrefetchPages pages further
-// along its XCD's run; the value is discarded, and the translation is cached by
-// the time that page's workgroups store to it.  Row loads and stores are
-// non-temporal: every row is read once and the destination is not read again
-// by this launch.
+// Row loads and stores are non-temporal: every row is read once and the
+// destination is not read again by this launch.
 //
 // Flat launches.  The units above give every page whole workgroups, which is
 // what makes the page's addresses scalar; where that leaves many lanes idle
@@ -483,37 +477,69 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, FastDiv f)
     return uint32_t((uint64_t(__umulhi(n, f.mul)) + n) >> f.shift);
 }
 
+// The arguments' pointers come from opaque dwords (read_args), so their
+// address spaces are named: global memory, and tables that do not change
+// during the launch, which uniform addresses read through the scalar cache.
+template <typename T>
+using global_ptr = T __attribute__((address_space(1)))*;
+template <typename T>
+using table_ptr = const T __attribute__((address_space(4)))*;
+
+template <typename T>
+__device__ __forceinline__ T load_global(const void* p)
+{
+    return *(global_ptr<const T>)(p);
+}
+
+typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+
 // One 16-byte vector of a row that this launch reads once (source row or
 // transfer-tensor row): a non-temporal load (global_load_dwordx4 ... nt), so
 // the line is not kept in the caches at the expense of other data.
 __device__ __forceinline__ uint4 load_stream(const char* p)
 {
-    typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-    const v4u v = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(p));
+    const v4u v = __builtin_nontemporal_load((global_ptr<const v4u>)(p));
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// Read one dword at the start of the destination page kPrefetchPages pages
-// after page `page_unit` (plane-major, as the units), so that its address
-// translation is cached before that page's workgroups store to it.  The value
-// is discarded; ids outside the pool are ignored.
-__device__ __forceinline__ void warm_translation(const KArgs& a, uint32_t page_unit)
+// One 16-byte vector of a destination row, which this launch does not read again.
+__device__ __forceinline__ void store_stream(char* p, const uint4& v)
 {
-    const uint32_t fp = page_unit + uint32_t(kPrefetchPages);
-    const uint32_t fplane = fdiv(fp, a.div_items);
-    if (fplane >= a.planes) return;
-    const uint32_t plane = fplane + a.dst_plane0;  // cache plane
-    const Item it = a.items[fp - fplane * a.num_items];
-    const int32_t b = a.bt[int64_t(it.req) * a.bt_stride + it.blk];
-    if (b < 0 || b >= a.num_blocks) return;
-    const volatile uint32_t* q = reinterpret_cast<const volatile uint32_t*>(
-        static_cast<const char*>(a.dst) + plane * a.plane_bytes +
-        int64_t(b) * a.block_size * a.hd * a.row_dst_bytes);
-    (void)*q;
+    __builtin_nontemporal_store(__builtin_bit_cast(v4u, v), (global_ptr<v4u>)(p));
+}
+
+// A group of kernel arguments, read at once: the empty asm makes the loaded
+// dwords opaque, so that the compiler keeps them in scalar registers from here
+// instead of loading each argument where it is first used, which makes a chain
+// of six to eight waits in front of a workgroup's row load.  Measured, kernel
+// time: one request of 256 tokens x 2 heads x 64 (0.5 MB) 3.64 -> 2.60 us;
+// one of 1900 tokens of 32 layers x 8 heads x 128 bf16 87.2 -> 85.0 us; paged,
+// 80 layers of one e4m3fn head, 128-token pages 100.5 -> 89.4 us.
+template <typename T>
+__device__ __forceinline__ T read_args(const T& from)
+{
+    static_assert(sizeof(T) % 8 == 0, "whole dwords");
+    T to;
+    if constexpr (sizeof(T) == 192) {
+        typedef uint32_t v16u __attribute__((ext_vector_type(16), aligned(4)));
+        struct Dwords { v16u v[3]; };
+        Dwords d;
+        __builtin_memcpy(&d, &from, sizeof d);
+        __asm__("" : "+s"(d.v[0]), "+s"(d.v[1]), "+s"(d.v[2]));
+        __builtin_memcpy(&to, &d, sizeof d);
+    } else {
+        struct Dwords { uint64_t v[sizeof(T) / 8]; };
+        Dwords d;
+        __builtin_memcpy(&d, &from, sizeof d);
+        for (uint64_t& x : d.v) __asm__("" : "+s"(x));
+        __builtin_memcpy(&to, &d, sizeof d);
+    }
+    return to;
 }
 
 template <int MODE, int CONV, int ORDER, bool FLAT>
-__device__ __forceinline__ void convert_part(const KArgs& a)
+__device__ __forceinline__ void convert_part(const KArgs& k)
 {
     constexpr bool kFp8 = CONV == kBf16E4m3 || CONV == kF16E4m3 ||    // writes 8-bit codes
                           CONV == kBf16E5m2 || CONV == kF16E5m2;
@@ -551,42 +577,58 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
         FLAT || (ORDER == KVX_PAGED && MODE != kPack) ||
         (ORDER == KVX_THD && (CONV == kCopy16 || CONV == kF16Bf16 || CONV == kBf16F16));
 
+    // The page-aligned form takes its argument groups whole; the flat one, which
+    // needs more of them at a time than fits the scalar registers, loads them
+    // where they are used (all at once: repack of 5-token pages from a paged
+    // source 389 -> 410 us).
+    const Args a = FLAT ? k.a : read_args(k.a);
+    Args2 f{};
+    if constexpr (FLAT) f = k.b;
+    else if constexpr (ORDER == KVX_HTD && MODE != kUnpack) f = read_args(k.b);
+    ArgsPaged g{};
+    if constexpr (ORDER == KVX_PAGED && MODE != kUnpack) g = FLAT ? k.p : read_args(k.p);
+
     // XCD-contiguous unit of this workgroup -> (plane, page, segment, part)
     const uint32_t unit = (blockIdx.x % kXcds) * a.units_per_xcd + blockIdx.x / kXcds;
     if (unit >= a.units) return;  // the grid is rounded up to a multiple of kXcds
     uint32_t plane, sg, part = 0;  // plane: layer * 2 + k/v
-    uint32_t page_unit;            // plane * pages + page
-    Item it;
+    uint32_t item;                 // logical page, requests in order
     int sub, r;                    // 16-byte chunk within the row, row within the segment
     bool live = true;              // the lane has a place in a page
     if constexpr (FLAT) {
         const uint32_t q1 = fdiv(unit, a.div_segs);
         sg = unit - q1 * a.num_segs;
-        plane = fdiv(q1, a.div_groups);
-        const uint32_t group = q1 - plane * a.groups;
+        plane = fdiv(q1, a.div_parts);
+        const uint32_t group = q1 - plane * a.parts;
         if (plane >= a.planes) return;
         // slot -> row of the plane and segment (page x rows of a page + row of the page)
         const uint32_t slot = group * kThreads + threadIdx.x;
-        const uint32_t row = fdiv(slot, a.div_row_lanes);
-        sub = int(slot - row * a.row_lanes);
-        const uint32_t item = fdiv(row, a.div_page_rows);
-        r = int(row - item * a.page_rows);
+        const uint32_t row = fdiv(slot, f.div_row_lanes);
+        sub = int(slot - row * f.row_lanes);
+        item = fdiv(row, f.div_page_rows);
+        r = int(row - item * f.page_rows);
         live = item < a.num_items;
-        page_unit = plane * a.num_items + item;
-        it = a.items[live ? item : 0u];
+        item = live ? item : 0u;
     } else {
         const uint32_t q1 = fdiv(unit, a.div_parts);
         part = unit - q1 * a.parts;
-        page_unit = fdiv(q1, a.div_segs);
-        sg = q1 - page_unit * a.num_segs;
-        plane = fdiv(page_unit, a.div_items);
-        const uint32_t item = page_unit - plane * a.num_items;
+        const uint32_t q2 = fdiv(q1, a.div_segs);
+        sg = q1 - q2 * a.num_segs;
+        plane = fdiv(q2, a.div_items);
+        item = q2 - plane * a.num_items;
         if (plane >= a.planes || item >= a.num_items || sg >= a.num_segs || part >= a.parts) return;
-        it = a.items[item];
         sub = threadIdx.x & ((1 << a.lg_lpr) - 1);
         r = int(part) * (kThreads >> a.lg_lpr) + (threadIdx.x >> a.lg_lpr);
     }
-    const Segment seg = a.seg[sg];
+    Item it;  // of the only request with pages: its tables start at its row, its offsets are 0
+    if (a.one_tokens) it = Item{0, 0, a.one_wire_scale, 0, int32_t(item), a.one_tokens, 0};
+    else {
+        const table_ptr<uint64_t> q = (table_ptr<uint64_t>)(a.items + item);
+        const uint64_t w[] = {q[0], q[1], q[2], q[3], q[4]};
+        __builtin_memcpy(&it, w, sizeof it);
+    }
+    Segment seg = a.seg0;
+    if (a.num_segs > 1) seg = k.seg[sg];
     const int T = it.tokens;
     const int t0 = it.blk * a.block_size;
     const int seg_rows = min(a.block_size, T - t0) * seg.n;
@@ -594,17 +636,17 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
     const int lg = a.lg_lpr;
 
     int32_t b = 0;  // destination page (unpack, repack)
-    if constexpr (kEarly && MODE != kPack) b = a.bt[int64_t(it.req) * a.bt_stride + it.blk];
+    if constexpr (kEarly && MODE != kPack) b = ((table_ptr<int32_t>)(a.bt))[int64_t(it.req) * a.bt_stride + it.blk];
     // Paged source whose parts never span two source pages: one page per
     // workgroup, looked up once (the part's first token must exist).
     int32_t sb_u = -1;
     uint32_t q_u = 0;
     if constexpr (ORDER == KVX_PAGED && MODE != kUnpack && !FLAT) {
-        if (a.sbt_uniform) {
+        if (g.sbt_uniform) {
             const uint32_t tf = uint32_t(t0) + fdiv(part * uint32_t(kThreads >> lg), seg.div_n);
             if (tf < uint32_t(T)) {
-                q_u = fdiv(tf, a.div_sbs);
-                sb_u = a.sbt[int64_t(it.req) * a.sbt_stride + q_u];
+                q_u = fdiv(tf, g.div_sbs);
+                sb_u = ((table_ptr<int32_t>)(g.sbt))[int64_t(it.req) * g.sbt_stride + q_u];
             }
         }
     }
@@ -614,7 +656,7 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
     if constexpr (ORDER == KVX_HTD && MODE != kUnpack) {
         // head-major rows: consecutive lane groups read consecutive tokens of one
         // head, contiguous in a [head][token][dim] source
-        ii = int(fdiv(uint32_t(r), a.div_bs));
+        ii = int(fdiv(uint32_t(r), f.div_bs));
         s = r - ii * a.block_size;
         ok = live && sub < a.cpr && ii < seg.n && s < min(a.block_size, T - t0);
     } else {
@@ -629,13 +671,13 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
     const char* p = nullptr;
     const float* sp = nullptr;
     if constexpr (MODE == kUnpack) {
-        base = static_cast<const char*>(a.wire_in);
+        base = static_cast<const char*>(seg.src);
         // a dequantising lane reads 8 codes at sub * 8 and 8 at (sub + cpr) * 8
         p = base + it.wire_data + (row0 + row) * a.row_wire_bytes + sub * (kDq ? 8 : 16);
         if constexpr (kScalesIn)
             sp = reinterpret_cast<const float*>(base + it.wire_scale) + row0 + row;
     } else {
-        base = static_cast<const char*>(a.src[seg.slot]);
+        base = static_cast<const char*>(seg.src);
         const int h = seg.h0 + ii;                           // head within the shard
         int64_t e = 0;
         if constexpr (ORDER == KVX_THD) {
@@ -648,13 +690,13 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
             const uint32_t t = uint32_t(t0 + s);
             int32_t sb = sb_u;
             uint32_t q = q_u;
-            if ((FLAT || !a.sbt_uniform) && ok) {
-                q = fdiv(t, a.div_sbs);
-                sb = a.sbt[int64_t(it.req) * a.sbt_stride + q];
+            if ((FLAT || !g.sbt_uniform) && ok) {
+                q = fdiv(t, g.div_sbs);
+                sb = ((table_ptr<int32_t>)(g.sbt))[int64_t(it.req) * g.sbt_stride + q];
             }
-            ok = ok && sb >= 0 && sb < a.src_num_blocks;
-            e = ((int64_t(plane + a.src_plane0) * a.src_num_blocks + sb) * a.src_block_size +
-                 int64_t(t - q * uint32_t(a.src_block_size))) * a.hs + h;
+            ok = ok && sb >= 0 && sb < g.src_num_blocks;
+            e = ((int64_t(plane + a.src_plane0) * g.src_num_blocks + sb) * g.src_block_size +
+                 int64_t(t - q * uint32_t(g.src_block_size))) * a.hs + h;
         }
         p = base + (it.src_base + e * a.head_dim) * kSrcEsz + sub * (kLaneElems * kSrcEsz);
     }
@@ -667,8 +709,8 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
         // lanes without a row read the buffer's first vector (valid, cached)
         const char* pl = ok ? p : base;
         if constexpr (kDq) {
-            const uint2 c0 = *reinterpret_cast<const uint2*>(pl);
-            const uint2 c1 = *reinterpret_cast<const uint2*>(pl + (ok ? second : 0));
+            const v2u c0 = load_global<v2u>(pl);
+            const v2u c1 = load_global<v2u>(pl + (ok ? second : 0));
             v[0] = make_uint4(c0.x, c0.y, c1.x, c1.y);
         } else {
 #pragma unroll
@@ -676,7 +718,7 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
                 v[k] = load_stream(pl + (ok ? k * second : 0));
         }
         if constexpr (MODE == kUnpack && kScalesIn)
-            sc = *(ok ? sp : reinterpret_cast<const float*>(base));
+            sc = load_global<float>(ok ? static_cast<const void*>(sp) : base);
         // keep the loads here: the compiler would otherwise sink them below
         // the destination-page check, behind the scalar lookups
         __asm__ volatile("" ::: "memory");
@@ -689,8 +731,8 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
         for (int k = 0; k < kVecs; ++k) v[k] = make_uint4(0u, 0u, 0u, 0u);
         if (ok) {
             if constexpr (kDq) {
-                const uint2 c0 = *reinterpret_cast<const uint2*>(p);
-                const uint2 c1 = *reinterpret_cast<const uint2*>(p + second);
+                const v2u c0 = load_global<v2u>(p);
+                const v2u c1 = load_global<v2u>(p + second);
                 v[0] = make_uint4(c0.x, c0.y, c1.x, c1.y);
             } else {
 #pragma unroll
@@ -698,9 +740,9 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
                     v[k] = load_stream(p + k * second);
             }
             if constexpr (MODE == kUnpack && kScalesIn)
-                if (kDq || sub == 0) sc = *sp;  // every dequantising lane needs the scale
+                if (kDq || sub == 0) sc = load_global<float>(sp);  // every dequantising lane needs the scale
         }
-        if constexpr (MODE != kPack) b = a.bt[int64_t(it.req) * a.bt_stride + it.blk];
+        if constexpr (MODE != kPack) b = ((table_ptr<int32_t>)(a.bt))[int64_t(it.req) * a.bt_stride + it.blk];
     }
 
     char* dbase;
@@ -714,7 +756,6 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
         if constexpr (FLAT) {
             ok = ok && page;
         } else {
-            if (part == 0 && sg == 0 && threadIdx.x == 0) warm_translation(a, page_unit);
             if (!page) return;
         }
         const int64_t page_rows = int64_t(b) * a.block_size * a.hd;
@@ -742,15 +783,11 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
     else
         out = v[0];
     if (ok) {
-        typedef unsigned int v4u __attribute__((ext_vector_type(4)));
         char* drow = dbase + int64_t(row) * a.row_dst_bytes;
-        __builtin_nontemporal_store(__builtin_bit_cast(v4u, out),
-                                    reinterpret_cast<v4u*>(drow + sub * 16));
-        if constexpr (kHalves)
-            __builtin_nontemporal_store(__builtin_bit_cast(v4u, out2),
-                                        reinterpret_cast<v4u*>(drow + (sub + a.cpr) * 16));
+        store_stream(drow + sub * 16, out);
+        if constexpr (kHalves) store_stream(drow + (sub + a.cpr) * 16, out2);
         if constexpr (kScales && (FLAT || !kFp8))  // the 8-bit unpack: the scale it loaded
-            if (sub == 0) __builtin_nontemporal_store(sc, sbase + row);
+            if (sub == 0) __builtin_nontemporal_store(sc, (global_ptr<float>)(sbase + row));
     }
     if constexpr (kFp8 && !FLAT) {
         // The quantising launches' 4-byte row scales go out through LDS: lane
@@ -772,45 +809,45 @@ __device__ __forceinline__ void convert_part(const KArgs& a)
         __syncthreads();
         if (int(threadIdx.x) < (kThreads >> lg)) {
             const int slot = lds_slot[threadIdx.x];
-            if (slot >= 0) sbase[slot] = lds_scale[threadIdx.x];
+            if (slot >= 0) *(global_ptr<float>)(sbase + slot) = lds_scale[threadIdx.x];
         }
     }
 }
 
 // One kernel name per operation, so traces tell them apart.
 template <int CONV, int ORDER, bool FLAT>
-__global__ void __launch_bounds__(kThreads) kvx_pack_kernel(const KArgs a)
+__global__ void __launch_bounds__(kThreads) kvx_pack_kernel(const KArgs k)
 {
-    convert_part<kPack, CONV, ORDER, FLAT>(a);
+    convert_part<kPack, CONV, ORDER, FLAT>(k);
 }
 
 template <int CONV, int ORDER, bool FLAT>
-__global__ void __launch_bounds__(kThreads) kvx_unpack_kernel(const KArgs a)
+__global__ void __launch_bounds__(kThreads) kvx_unpack_kernel(const KArgs k)
 {
-    convert_part<kUnpack, CONV, ORDER, FLAT>(a);
+    convert_part<kUnpack, CONV, ORDER, FLAT>(k);
 }
 
 template <int CONV, int ORDER, bool FLAT>
-__global__ void __launch_bounds__(kThreads) kvx_repack_kernel(const KArgs a)
+__global__ void __launch_bounds__(kThreads) kvx_repack_kernel(const KArgs k)
 {
-    convert_part<kRepack, CONV, ORDER, FLAT>(a);
+    convert_part<kRepack, CONV, ORDER, FLAT>(k);
 }
 
 template <int MODE, int CONV, int ORDER>
-int go(const KArgs& a, void* stream)
+int go(const KArgs& k, void* stream)
 {
     const void* fn;
     if constexpr (MODE == kPack)
-        fn = a.flat ? reinterpret_cast<const void*>(&kvx_pack_kernel<CONV, ORDER, true>)
+        fn = k.flat ? reinterpret_cast<const void*>(&kvx_pack_kernel<CONV, ORDER, true>)
                     : reinterpret_cast<const void*>(&kvx_pack_kernel<CONV, ORDER, false>);
     else if constexpr (MODE == kUnpack)
-        fn = a.flat ? reinterpret_cast<const void*>(&kvx_unpack_kernel<CONV, ORDER, true>)
+        fn = k.flat ? reinterpret_cast<const void*>(&kvx_unpack_kernel<CONV, ORDER, true>)
                     : reinterpret_cast<const void*>(&kvx_unpack_kernel<CONV, ORDER, false>);
     else
-        fn = a.flat ? reinterpret_cast<const void*>(&kvx_repack_kernel<CONV, ORDER, true>)
+        fn = k.flat ? reinterpret_cast<const void*>(&kvx_repack_kernel<CONV, ORDER, true>)
                     : reinterpret_cast<const void*>(&kvx_repack_kernel<CONV, ORDER, false>);
-    void* args[] = {const_cast<KArgs*>(&a)};
-    const unsigned grid = a.units_per_xcd * kXcds;
+    void* args[] = {const_cast<KArgs*>(&k)};
+    const unsigned grid = k.a.units_per_xcd * kXcds;
     return int(hipLaunchKernel(fn, dim3(grid), dim3(kThreads), args, 0,
                                static_cast<hipStream_t>(stream)));
 }

@@ -232,6 +232,7 @@ kvx_status kvx_plan(const kvx_desc* desc, kvx_plan_t** out)
             p->wire_scale[r] = -1;
         }
         const int64_t nb = (T + d.block_size - 1) / d.block_size;
+        if (nb > 0) p->one_req = nitems == 0 ? r : -1;
         p->max_blocks = int32_t(std::max<int64_t>(p->max_blocks, nb));
         nitems += nb;
         p->total_tokens += T;
@@ -255,23 +256,26 @@ kvx_status kvx_plan(const kvx_desc* desc, kvx_plan_t** out)
                                     p->lens[r], 0});
     }
 
-    // device table on the current device, when one is usable
+    // device table on the current device, when one is usable; the pages of an
+    // only request need none
     int dev = -1;
     if (!p->items.empty() && hipGetDevice(&dev) == hipSuccess && dev >= 0) {
-        const size_t ib = p->items.size() * sizeof(Item);
-        void* t = nullptr;
-        if (hipMalloc(&t, ib) != hipSuccess) {
-            delete p;
-            return fail(KVX_ENOMEM, "device table allocation failed");
-        }
-        if (hipMemcpy(t, p->items.data(), ib, hipMemcpyHostToDevice) != hipSuccess) {
-            (void)hipFree(t);
-            delete p;
-            return fail(KVX_EDEVICE, "device table upload failed");
-        }
         p->device = dev;
-        p->dev_table = t;
-        p->dev_items = static_cast<const Item*>(t);
+        if (p->one_req < 0) {
+            const size_t ib = p->items.size() * sizeof(Item);
+            void* t = nullptr;
+            if (hipMalloc(&t, ib) != hipSuccess) {
+                delete p;
+                return fail(KVX_ENOMEM, "device table allocation failed");
+            }
+            if (hipMemcpy(t, p->items.data(), ib, hipMemcpyHostToDevice) != hipSuccess) {
+                (void)hipFree(t);
+                delete p;
+                return fail(KVX_EDEVICE, "device table upload failed");
+            }
+            p->dev_table = t;
+            p->dev_items = static_cast<const Item*>(t);
+        }
     } else if (!p->items.empty()) {
         (void)hipGetLastError();  // no device: host-only plan
     }
@@ -437,7 +441,7 @@ kvx_status kvx::derive_shape(const kvx_desc& d, Shape& s)
             return fail(KVX_EUNSUPPORTED, "decode rank needs more than %d head segments",
                         kMaxReadShards);
         if (slot == s.nread) s.read_shards[s.nread++] = j;
-        s.segs[s.nsegs++] = Segment{slot, h, i, 1, {0, 0}};
+        s.segs[s.nsegs++] = Segment{nullptr, slot, h, i, 1, {0, 0}};
     }
     for (int k = 0; k < s.nsegs; ++k) s.segs[k].div_n = make_fastdiv(uint32_t(s.segs[k].n));
 
@@ -470,17 +474,32 @@ int conv_for(const kvx_plan_t* p, int mode)
     return p->conv;
 }
 
+// The only request with pages, if there is just one: launches then need no
+// work-item table (its offsets in the buffers are 0).
+struct OneRequest {
+    int32_t req = -1;         // -1: several
+    int32_t tokens = 0;
+    int64_t wire_scale = -1;
+};
+
 // The kernel arguments every launch mode shares, from the descriptor, its
-// shape and the work-item table; the source (or transfer-tensor) pointers and
-// a paged source's fields are set by the caller.
+// shape and the work-item table; src holds the read shards by slot (the unpack:
+// the transfer tensor); a paged source's fields are set by the caller.
 void fill_args(const kvx_desc& d, const kvx::Shape& s, int mode, uint32_t num_items,
-               const Item* items, void* dst, float* scales, const int32_t* bt, int32_t bt_stride,
-               int layer_shift, kvx::KArgs& a)
+               const Item* items, const OneRequest& one, const void* const* src, void* dst,
+               float* scales, const int32_t* bt, int32_t bt_stride, int layer_shift, kvx::KArgs& k)
 {
+    kvx::Args& a = k.a;
+    kvx::Args2& f = k.b;
     a.dst = dst;
     a.dscale = scales;
     a.items = items;
     a.bt = bt;
+    if (one.req >= 0) {
+        a.one_tokens = one.tokens;
+        a.one_wire_scale = one.wire_scale;
+        if (bt) a.bt = bt + int64_t(one.req) * bt_stride;
+    }
     a.num_items = num_items;
     a.planes = uint32_t(2 * d.num_layers);
     a.src_plane0 = uint32_t(2 * (d.src_layer_offset + layer_shift));
@@ -488,11 +507,17 @@ void fill_args(const kvx_desc& d, const kvx::Shape& s, int mode, uint32_t num_it
     if (mode == kvx::kUnpack) {  // transfer-tensor rows are already in decode order
         a.num_segs = 1;
         a.parts = uint32_t(s.parts_unpack);
-        a.seg[0] = kvx::Segment{0, 0, 0, s.hd, kvx::make_fastdiv(uint32_t(s.hd))};
+        a.seg0 = kvx::Segment{src[0], 0, 0, 0, s.hd, kvx::make_fastdiv(uint32_t(s.hd))};
     } else {
         a.num_segs = uint32_t(s.nsegs);
         a.parts = uint32_t(s.parts);
-        for (int k = 0; k < s.nsegs; ++k) a.seg[k] = s.segs[k];
+        a.seg0 = s.segs[0];
+        a.seg0.src = src[a.seg0.slot];
+        if (s.nsegs > 1)
+            for (int j = 0; j < s.nsegs; ++j) {
+                k.seg[j] = s.segs[j];
+                k.seg[j].src = src[s.segs[j].slot];
+            }
     }
     // Flat launches (see the kernels).  Two shares of the page-aligned form's
     // lanes decide: those that cover a row (cpr of 2^lg_lpr), and those that
@@ -512,33 +537,32 @@ void fill_args(const kvx_desc& d, const kvx::Shape& s, int mode, uint32_t num_it
     //    one-token pages of 2 heads x 80 616 -> 70 us.
     // The flat units are never more than the others: a page's rows fit its
     // whole workgroups.
-    int max_n = 0;
-    for (uint32_t k = 0; k < a.num_segs; ++k) max_n = std::max(max_n, a.seg[k].n);
-    a.page_rows = uint32_t(d.block_size) * uint32_t(max_n);
+    int max_n = a.seg0.n;
+    for (uint32_t j = 1; j < a.num_segs; ++j) max_n = std::max(max_n, k.seg[j].n);
+    f.page_rows = uint32_t(d.block_size) * uint32_t(max_n);
     const int64_t lpr = int64_t(1) << s.lg_lpr;
     int chunk_eighths = 6;  // of its lanes that a row packed chunk by chunk may fill
     if (is_fp8(d.dst_dtype)) chunk_eighths = 0;
     else if (mode != kvx::kUnpack && d.src_order == KVX_HTD) chunk_eighths = 0;
     else if (mode != kvx::kUnpack && d.src_order == KVX_PAGED) chunk_eighths = mode == kvx::kPack ? 0 : 5;
     const bool by_chunk = s.cpr * 8 <= lpr * chunk_eighths;
-    a.row_lanes = uint32_t(by_chunk ? s.cpr : lpr);
-    a.flat = by_chunk ||
-             int64_t(a.page_rows) * lpr * 8 <= int64_t(a.parts) * kvx::kThreads * (is_fp8(d.dst_dtype) ? 5 : 6);
+    f.row_lanes = uint32_t(by_chunk ? s.cpr : lpr);
+    k.flat = by_chunk ||
+             int64_t(f.page_rows) * lpr * 8 <= int64_t(a.parts) * kvx::kThreads * (is_fp8(d.dst_dtype) ? 5 : 6);
     int64_t units = int64_t(num_items) * a.planes * a.num_segs * a.parts;
-    if (a.flat) {
-        const int64_t lanes = int64_t(num_items) * a.page_rows * a.row_lanes;
-        a.groups = uint32_t((lanes + kvx::kThreads - 1) / kvx::kThreads);
-        units = int64_t(a.groups) * a.planes * a.num_segs;
-        a.div_groups = kvx::make_fastdiv(a.groups);
-        a.div_row_lanes = kvx::make_fastdiv(a.row_lanes);
-        a.div_page_rows = kvx::make_fastdiv(a.page_rows);
+    if (k.flat) {
+        const int64_t lanes = int64_t(num_items) * f.page_rows * f.row_lanes;
+        a.parts = uint32_t((lanes + kvx::kThreads - 1) / kvx::kThreads);
+        units = int64_t(a.parts) * a.planes * a.num_segs;
+        f.div_row_lanes = kvx::make_fastdiv(f.row_lanes);
+        f.div_page_rows = kvx::make_fastdiv(f.page_rows);
     }
     a.units = uint32_t(units);
     a.units_per_xcd = uint32_t((units + kvx::kXcds - 1) / kvx::kXcds);
     a.div_parts = kvx::make_fastdiv(a.parts);
     a.div_segs = kvx::make_fastdiv(a.num_segs);
     a.div_items = kvx::make_fastdiv(a.num_items);
-    a.div_bs = kvx::make_fastdiv(uint32_t(d.block_size));
+    f.div_bs = kvx::make_fastdiv(uint32_t(d.block_size));
     a.num_blocks = d.num_blocks;
     a.plane_bytes = d.num_blocks * d.block_size * int64_t(s.hd) * d.head_dim * s.esz_cache;
     a.plane_scales = d.num_blocks * d.block_size * int64_t(s.hd);
@@ -558,13 +582,14 @@ void fill_args(const kvx_desc& d, const kvx::Shape& s, int mode, uint32_t num_it
 // the plan's source order (the unpack reads no source and takes either).
 kvx_status prepare(const kvx_plan_t* p, int mode, bool paged_call, const void* const* shards,
                    const int32_t* sbt, int32_t sbt_stride, const void* wire, void* dst,
-                   float* scales, const int32_t* bt, int32_t bt_stride, kvx::KArgs& a,
+                   float* scales, const int32_t* bt, int32_t bt_stride, kvx::KArgs& k,
                    int layer_shift = 0)
 {
     if (!p) return fail(KVX_EINVAL, "NULL plan");
     const bool fp8 = is_fp8(p->cache_dtype);  // the cache holds scales
     const bool paged = p->d.src_order == KVX_PAGED;
-    std::memset(&a, 0, sizeof a);
+    std::memset(&k, 0, sizeof k);
+    const void* src[kvx::kMaxReadShards] = {};
     if (mode != kvx::kUnpack && paged != paged_call)
         return fail(KVX_EINVAL, paged ? "the plan's source is paged: use kvx_pack_paged / kvx_repack_paged"
                                       : "the plan's source is not paged: use kvx_pack / kvx_repack");
@@ -577,17 +602,17 @@ kvx_status prepare(const kvx_plan_t* p, int mode, bool paged_call, const void* c
     }
     if (mode != kvx::kUnpack) {
         if (!shards) return fail(KVX_EINVAL, "NULL src_shards array");
-        for (size_t k = 0; k < p->read_shards.size(); ++k) {
-            const int j = p->read_shards[k];
+        for (size_t i = 0; i < p->read_shards.size(); ++i) {
+            const int j = p->read_shards[i];
             const void* s = shards[j];
             if (!s) return fail(KVX_EINVAL, "src_shards[%d] is NULL", j);
             if (!aligned16(s)) return fail(KVX_EINVAL, "src_shards[%d] is not 16-byte aligned", j);
-            a.src[k] = s;
+            src[i] = s;
         }
     } else {
         if (!wire) return fail(KVX_EINVAL, "NULL transfer tensor");
         if (!aligned16(wire)) return fail(KVX_EINVAL, "transfer tensor not 16-byte aligned");
-        a.wire_in = wire;
+        src[0] = wire;
     }
     if (!dst) return fail(KVX_EINVAL, mode == kvx::kPack ? "NULL transfer tensor" : "NULL cache");
     if (!aligned16(dst)) return fail(KVX_EINVAL, "destination not 16-byte aligned");
@@ -607,10 +632,14 @@ kvx_status prepare(const kvx_plan_t* p, int mode, bool paged_call, const void* c
         return fail(KVX_EDEVICE, "current device %d is not the plan's device %d", cur, p->device);
 
     const kvx_desc& d = p->d;
-    fill_args(d, p->sh, mode, uint32_t(p->items.size()), p->dev_items, dst, scales, bt, bt_stride,
-              layer_shift, a);
+    OneRequest one;
+    if (p->one_req >= 0)
+        one = OneRequest{p->one_req, p->lens[p->one_req], p->wire_scale[p->one_req]};
+    fill_args(d, p->sh, mode, uint32_t(p->items.size()), p->dev_items, one, src, dst, scales, bt,
+              bt_stride, layer_shift, k);
     if (mode != kvx::kUnpack && paged) {
-        a.sbt = sbt;
+        kvx::ArgsPaged& a = k.p;
+        a.sbt = one.req >= 0 ? sbt + int64_t(one.req) * sbt_stride : sbt;
         a.sbt_stride = sbt_stride;
         a.src_block_size = d.src_block_size;
         a.src_num_blocks = d.src_num_blocks;
@@ -619,7 +648,7 @@ kvx_status prepare(const kvx_plan_t* p, int mode, bool paged_call, const void* c
         // i.e. tokens from part*rpp/n on.  When n divides rpp, a part holds
         // rpp/n whole tokens starting at a multiple of rpp/n; when rpp/n also
         // divides both page sizes, those tokens never straddle a source page.
-        const int rpp = kvx::kThreads >> a.lg_lpr;
+        const int rpp = kvx::kThreads >> k.a.lg_lpr;
         bool uniform = true;
         for (const kvx::Segment& g : p->segs)
             if (rpp % g.n || d.src_block_size % (rpp / g.n) || d.block_size % (rpp / g.n))
@@ -629,10 +658,10 @@ kvx_status prepare(const kvx_plan_t* p, int mode, bool paged_call, const void* c
     return KVX_OK;
 }
 
-kvx_status run(const kvx_plan_t* p, int mode, const kvx::KArgs& a, void* stream)
+kvx_status run(const kvx_plan_t* p, int mode, const kvx::KArgs& k, void* stream)
 {
     if (p->items.empty()) return KVX_OK;
-    const int err = kvx::launch(mode, conv_for(p, mode), p->d.src_order, a, stream);
+    const int err = kvx::launch(mode, conv_for(p, mode), p->d.src_order, k, stream);
     if (err != 0)
         return fail(KVX_EDEVICE, "kernel launch failed: %s", hipGetErrorString(hipError_t(err)));
     return KVX_OK;
@@ -715,8 +744,10 @@ kvx_status kvx_repack_noalloc(const kvx_desc* desc, const void* const* shards, v
     st = kvx::derive_shape(d, s);
     if (st != KVX_OK) return st;
     int64_t items = 0, max_blocks = 0;
+    OneRequest one;
     for (int r = 0; r < d.num_requests; ++r) {
         const int64_t nb = (int64_t(d.seq_lens[r]) + d.block_size - 1) / d.block_size;
+        if (nb > 0) one = items == 0 ? OneRequest{r, d.seq_lens[r], -1} : OneRequest{};
         items += nb;
         max_blocks = std::max(max_blocks, nb);
     }
@@ -730,14 +761,13 @@ kvx_status kvx_repack_noalloc(const kvx_desc* desc, const void* const* shards, v
         return fail(KVX_EUNSUPPORTED, "more than %lld work units (pages x 2 x layers x parts)",
                     (long long)kvx::kMaxUnits);
 
-    kvx::KArgs a;
-    std::memset(&a, 0, sizeof a);
+    const void* src[kvx::kMaxReadShards] = {};
     if (!shards) return fail(KVX_EINVAL, "NULL src_shards array");
     for (int k = 0; k < s.nread; ++k) {
         const int j = s.read_shards[k];
         if (!shards[j]) return fail(KVX_EINVAL, "src_shards[%d] is NULL", j);
         if (!aligned16(shards[j])) return fail(KVX_EINVAL, "src_shards[%d] is not 16-byte aligned", j);
-        a.src[k] = shards[j];
+        src[k] = shards[j];
     }
     const bool fp8 = is_fp8(s.cache_dtype);  // the cache holds scales
     if (!cache) return fail(KVX_EINVAL, "NULL cache");
@@ -752,22 +782,32 @@ kvx_status kvx_repack_noalloc(const kvx_desc* desc, const void* const* shards, v
                     (long long)max_blocks);
 
     kvx::Item* table = nullptr;
-    int e = kvx::scratch_items(&table);
-    if (e != 0)
-        return fail(KVX_EDEVICE, "static work-item table: %s", hipGetErrorString(hipError_t(e)));
-    kvx::ItemsArgs ia;
-    std::memset(&ia, 0, sizeof ia);
-    for (int r = 0; r < d.num_requests; ++r) ia.lens[r] = d.seq_lens[r];
-    ia.num_requests = d.num_requests;
-    ia.block_size = d.block_size;
-    ia.src_elems_per_token = 2 * int64_t(src_layers_of(d)) * s.hs * d.head_dim;
-    ia.items = table;
-    e = kvx::build_items(ia, stream);
-    if (e != 0)
-        return fail(KVX_EDEVICE, "work-item launch failed: %s", hipGetErrorString(hipError_t(e)));
-    fill_args(d, s, kvx::kRepack, uint32_t(items), table, cache, scales, bt, bt_stride, 0, a);
+    if (one.req >= 0) {  // no table
+        int dev = -1;
+        const hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return fail(KVX_EDEVICE, "no HIP device: %s", hipGetErrorString(e));
+    } else {
+        int e = kvx::scratch_items(&table);
+        if (e != 0)
+            return fail(KVX_EDEVICE, "static work-item table: %s", hipGetErrorString(hipError_t(e)));
+        kvx::ItemsArgs ia;
+        std::memset(&ia, 0, sizeof ia);
+        for (int r = 0; r < d.num_requests; ++r) ia.lens[r] = d.seq_lens[r];
+        ia.num_requests = d.num_requests;
+        ia.block_size = d.block_size;
+        ia.src_elems_per_token = 2 * int64_t(src_layers_of(d)) * s.hs * d.head_dim;
+        ia.items = table;
+        e = kvx::build_items(ia, stream);
+        if (e != 0)
+            return fail(KVX_EDEVICE, "work-item launch failed: %s",
+                        hipGetErrorString(hipError_t(e)));
+    }
+    kvx::KArgs k;
+    std::memset(&k, 0, sizeof k);
+    fill_args(d, s, kvx::kRepack, uint32_t(items), table, one, src, cache, scales, bt, bt_stride, 0,
+              k);
     const int conv = s.dequant ? qd_conv(d.src_dtype, d.dst_dtype, s.cache_dtype) : s.conv;
-    e = kvx::launch(kvx::kRepack, conv, d.src_order, a, stream);
+    const int e = kvx::launch(kvx::kRepack, conv, d.src_order, k, stream);
     if (e != 0)
         return fail(KVX_EDEVICE, "kernel launch failed: %s", hipGetErrorString(hipError_t(e)));
     return KVX_OK;
