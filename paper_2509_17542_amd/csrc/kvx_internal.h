@@ -77,6 +77,13 @@ struct Segment {
     FastDiv div_n;
 };
 
+// Cache policy of the destination rows' stores.
+enum Store : int { kStoreStream = 0, kStoreThrough = 1, kStoreCached = 2 };
+
+// Units of page-aligned workgroups, or the rows of consecutive pages packed
+// into workgroups, written with kStoreStream or kStoreCached.
+enum Form : int { kAligned = 0, kFlat = 1, kFlatCached = 2 };
+
 // Kernel arguments (passed by value through the kernel-argument segment).  A
 // kernel reads the groups that its form needs whole, at its start, so that one
 // wait covers them all: Args, then Args2 (head-major, flat and 8-bit forms)
@@ -98,7 +105,8 @@ struct Args {
     int32_t hd;                       // heads per decode rank
     int32_t head_dim;
     int32_t cpr;                      // 16-byte transfer-tensor chunks per row
-    int32_t lg_lpr;                   // log2(lanes per row), lanes per row >= cpr
+    int16_t lg_lpr;                   // log2(lanes per row), lanes per row >= cpr
+    int16_t store;                    // Store: how destination rows are written (kAligned)
     int32_t row_dst_bytes;            // pack: transfer-tensor row bytes; else cache row bytes
     uint32_t src_plane0;              // 2 x source layer offset (pipeline stages)
     uint32_t dst_plane0;              // 2 x cache layer offset
@@ -135,7 +143,7 @@ struct KArgs {
     Args a;
     Args2 b;
     ArgsPaged p;
-    int32_t flat;                     // the launch is flat (read by the host)
+    int32_t form;                     // Form: which kernel (read by the host)
     int32_t pad;
     Segment seg[kMaxReadShards];      // pack/repack: the head segments; unpack: one, all heads
 };

@@ -503,10 +503,31 @@ __device__ __forceinline__ uint4 load_stream(const char* p)
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// One 16-byte vector of a destination row, which this launch does not read again.
-__device__ __forceinline__ void store_stream(char* p, const uint4& v)
+// One 16-byte vector of a destination row, or two (N of them), which this
+// launch does not read again: non-temporal (kStoreStream), non-temporal and
+// written through the L2 (kStoreThrough), or kept in the L2 until its line is
+// whole (kStoreCached); the planner's rule has the sizes of each.  The two
+// vectors of a lane are stored back to back (a choice between each: 64-byte
+// half rows 144 -> 165 us).  The flat forms fix theirs at compile time, where
+// a choice at run time costs 1-4%.  The assembly form holds the two
+// wait states that a 16-byte store needs before its data registers are
+// written again, which the compiler cannot see in assembly.
+template <int N, int FORM>
+__device__ __forceinline__ void store_rows(char* const (&p)[N], const uint4 (&v)[N], int store)
 {
-    __builtin_nontemporal_store(__builtin_bit_cast(v4u, v), (global_ptr<v4u>)(p));
+    if (FORM == kAligned && store == kStoreThrough) {
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            __asm__ volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 1"
+                             : : "v"(p[i]), "v"(__builtin_bit_cast(v4u, v[i])) : "memory");
+    } else if (FORM == kFlat || (FORM == kAligned && store == kStoreStream)) {
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            __builtin_nontemporal_store(__builtin_bit_cast(v4u, v[i]), (global_ptr<v4u>)(p[i]));
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) *(global_ptr<v4u>)(p[i]) = __builtin_bit_cast(v4u, v[i]);
+    }
 }
 
 // A group of kernel arguments, read at once: the empty asm makes the loaded
@@ -538,9 +559,10 @@ __device__ __forceinline__ T read_args(const T& from)
     return to;
 }
 
-template <int MODE, int CONV, int ORDER, bool FLAT>
+template <int MODE, int CONV, int ORDER, int FORM>
 __device__ __forceinline__ void convert_part(const KArgs& k)
 {
+    constexpr bool FLAT = FORM != kAligned;
     constexpr bool kFp8 = CONV == kBf16E4m3 || CONV == kF16E4m3 ||    // writes 8-bit codes
                           CONV == kBf16E5m2 || CONV == kF16E5m2;
     constexpr bool kQd = CONV == kQdBf16Bf16 || CONV == kQdF16Bf16 ||  // quantise + dequantise
@@ -784,8 +806,10 @@ __device__ __forceinline__ void convert_part(const KArgs& k)
         out = v[0];
     if (ok) {
         char* drow = dbase + int64_t(row) * a.row_dst_bytes;
-        store_stream(drow + sub * 16, out);
-        if constexpr (kHalves) store_stream(drow + (sub + a.cpr) * 16, out2);
+        if constexpr (kHalves)
+            store_rows<2, FORM>({drow + sub * 16, drow + (sub + a.cpr) * 16}, {out, out2}, a.store);
+        else
+            store_rows<1, FORM>({drow + sub * 16}, {out}, a.store);
         if constexpr (kScales && (FLAT || !kFp8))  // the 8-bit unpack: the scale it loaded
             if (sub == 0) __builtin_nontemporal_store(sc, (global_ptr<float>)(sbase + row));
     }
@@ -815,37 +839,41 @@ __device__ __forceinline__ void convert_part(const KArgs& k)
 }
 
 // One kernel name per operation, so traces tell them apart.
-template <int CONV, int ORDER, bool FLAT>
+template <int CONV, int ORDER, int FORM>
 __global__ void __launch_bounds__(kThreads) kvx_pack_kernel(const KArgs k)
 {
-    convert_part<kPack, CONV, ORDER, FLAT>(k);
+    convert_part<kPack, CONV, ORDER, FORM>(k);
 }
 
-template <int CONV, int ORDER, bool FLAT>
+template <int CONV, int ORDER, int FORM>
 __global__ void __launch_bounds__(kThreads) kvx_unpack_kernel(const KArgs k)
 {
-    convert_part<kUnpack, CONV, ORDER, FLAT>(k);
+    convert_part<kUnpack, CONV, ORDER, FORM>(k);
 }
 
-template <int CONV, int ORDER, bool FLAT>
+template <int CONV, int ORDER, int FORM>
 __global__ void __launch_bounds__(kThreads) kvx_repack_kernel(const KArgs k)
 {
-    convert_part<kRepack, CONV, ORDER, FLAT>(k);
+    convert_part<kRepack, CONV, ORDER, FORM>(k);
+}
+
+template <int MODE, int CONV, int ORDER, int FORM>
+const void* kernel()
+{
+    if constexpr (MODE == kPack)
+        return reinterpret_cast<const void*>(&kvx_pack_kernel<CONV, ORDER, FORM>);
+    else if constexpr (MODE == kUnpack)
+        return reinterpret_cast<const void*>(&kvx_unpack_kernel<CONV, ORDER, FORM>);
+    else
+        return reinterpret_cast<const void*>(&kvx_repack_kernel<CONV, ORDER, FORM>);
 }
 
 template <int MODE, int CONV, int ORDER>
 int go(const KArgs& k, void* stream)
 {
-    const void* fn;
-    if constexpr (MODE == kPack)
-        fn = k.flat ? reinterpret_cast<const void*>(&kvx_pack_kernel<CONV, ORDER, true>)
-                    : reinterpret_cast<const void*>(&kvx_pack_kernel<CONV, ORDER, false>);
-    else if constexpr (MODE == kUnpack)
-        fn = k.flat ? reinterpret_cast<const void*>(&kvx_unpack_kernel<CONV, ORDER, true>)
-                    : reinterpret_cast<const void*>(&kvx_unpack_kernel<CONV, ORDER, false>);
-    else
-        fn = k.flat ? reinterpret_cast<const void*>(&kvx_repack_kernel<CONV, ORDER, true>)
-                    : reinterpret_cast<const void*>(&kvx_repack_kernel<CONV, ORDER, false>);
+    const void* const fn = k.form == kAligned  ? kernel<MODE, CONV, ORDER, kAligned>()
+                           : k.form == kFlat ? kernel<MODE, CONV, ORDER, kFlat>()
+                                             : kernel<MODE, CONV, ORDER, kFlatCached>();
     void* args[] = {const_cast<KArgs*>(&k)};
     const unsigned grid = k.a.units_per_xcd * kXcds;
     return int(hipLaunchKernel(fn, dim3(grid), dim3(kThreads), args, 0,

@@ -482,6 +482,51 @@ struct OneRequest {
     int64_t wire_scale = -1;
 };
 
+// How the launch writes its destination rows, by the bytes that one store
+// instruction of a wave covers in one piece: the rows that its lanes hold where
+// those follow one another in the destination, else those of one token's heads,
+// or one row; half a row where a dequantising lane writes each half by itself.
+//  - Pieces that are not whole 64-byte sectors leave parts of a sector to
+//    another instruction: the L2 merges them (kStoreCached).  160-byte rows
+//    of a head-major source 295 -> 273 us, 112-byte half rows 341 -> 270, 160-
+//    byte rows at 320 72 -> 58; written through they take 418, 634 and 90.
+//    Long pieces (512 bytes on) meet at few of their sectors and stream.
+//  - Whole sectors stream past the caches.  Written through the L2 as well
+//    they reach memory in the order of the launch: packs 3% faster (14266
+//    tokens, 128 KB each: 580 -> 562 us; 1900 tokens 78.2 -> 75.4), 64 KB pages
+//    578 -> 563, head-major 344.5 -> 337, paged to 64 KB pages 342.5 -> 335; but
+//    a cache's 32 KB pages below the 256 MB that the memory-side cache holds
+//    run up to 1% slower so, and so do the shortest pieces (64-byte ones 144
+//    -> 150, 128-byte half rows 272 -> 274) and packs whose tokens do not
+//    start at a sector (one head of 224 bytes: 184 -> 196).
+int store_policy(const kvx_desc& d, const kvx::Shape& s, int mode, const kvx::KArgs& k,
+                 int flat_row_lanes, int64_t num_items)
+{
+    const kvx::Args& a = k.a;
+    const bool halves = s.dequant && mode != kvx::kPack;
+    // (a head-major source's rows of one head: the next token's follows where it is the only one)
+    const bool head_major = mode != kvx::kUnpack && d.src_order == KVX_HTD && s.hd > 1;
+    int64_t piece = a.row_dst_bytes;
+    if (halves) piece /= 2;
+    else if (a.num_segs == 1 && !head_major)
+        piece = flat_row_lanes == s.cpr ? 1024 : (64 >> s.lg_lpr) * piece;
+    else if (!head_major) {
+        const int64_t row = piece;
+        piece = a.seg0.n * row;
+        for (uint32_t j = 1; j < a.num_segs; ++j)  // the smallest, a broken sector first
+            if (k.seg[j].n * row % 64 || (piece % 64 == 0 && k.seg[j].n * row < piece))
+                piece = k.seg[j].n * row;
+    }
+    // the runs of rows that the pieces are cut from start in whole sectors too:
+    // the pages of the cache, the tokens of the transfer tensor
+    const int64_t run = int64_t(s.hd) * a.row_dst_bytes * (mode == kvx::kPack ? 1 : d.block_size);
+    if (piece % 64 || run % 64) return piece < 512 ? kvx::kStoreCached : kvx::kStoreStream;
+    if (flat_row_lanes || piece < (halves ? 192 : 128)) return kvx::kStoreStream;
+    if (mode == kvx::kPack) return kvx::kStoreThrough;
+    const int64_t bytes = num_items * d.block_size * a.planes * s.hd * int64_t(a.row_dst_bytes);
+    return bytes > (int64_t(256) << 20) ? kvx::kStoreThrough : kvx::kStoreStream;
+}
+
 // The kernel arguments every launch mode shares, from the descriptor, its
 // shape and the work-item table; src holds the read shards by slot (the unpack:
 // the transfer tensor); a paged source's fields are set by the caller.
@@ -543,14 +588,14 @@ void fill_args(const kvx_desc& d, const kvx::Shape& s, int mode, uint32_t num_it
     const int64_t lpr = int64_t(1) << s.lg_lpr;
     int chunk_eighths = 6;  // of its lanes that a row packed chunk by chunk may fill
     if (is_fp8(d.dst_dtype)) chunk_eighths = 0;
-    else if (mode != kvx::kUnpack && d.src_order == KVX_HTD) chunk_eighths = 0;
+    else if (mode != kvx::kUnpack && d.src_order == KVX_HTD && max_n > 1) chunk_eighths = 0;
     else if (mode != kvx::kUnpack && d.src_order == KVX_PAGED) chunk_eighths = mode == kvx::kPack ? 0 : 5;
     const bool by_chunk = s.cpr * 8 <= lpr * chunk_eighths;
     f.row_lanes = uint32_t(by_chunk ? s.cpr : lpr);
-    k.flat = by_chunk ||
-             int64_t(f.page_rows) * lpr * 8 <= int64_t(a.parts) * kvx::kThreads * (is_fp8(d.dst_dtype) ? 5 : 6);
+    const bool flat = by_chunk || int64_t(f.page_rows) * lpr * 8 <=
+                                      int64_t(a.parts) * kvx::kThreads * (is_fp8(d.dst_dtype) ? 5 : 6);
     int64_t units = int64_t(num_items) * a.planes * a.num_segs * a.parts;
-    if (k.flat) {
+    if (flat) {
         const int64_t lanes = int64_t(num_items) * f.page_rows * f.row_lanes;
         a.parts = uint32_t((lanes + kvx::kThreads - 1) / kvx::kThreads);
         units = int64_t(a.parts) * a.planes * a.num_segs;
@@ -574,7 +619,10 @@ void fill_args(const kvx_desc& d, const kvx::Shape& s, int mode, uint32_t num_it
     a.row_wire_bytes = d.head_dim * s.esz_dst;
     a.row_dst_bytes = mode == kvx::kPack ? a.row_wire_bytes : d.head_dim * s.esz_cache;
     a.cpr = s.cpr;
-    a.lg_lpr = s.lg_lpr;
+    a.lg_lpr = int16_t(s.lg_lpr);
+    const int store = store_policy(d, s, mode, k, flat ? int(f.row_lanes) : 0, num_items);
+    a.store = int16_t(store);
+    k.form = !flat ? kvx::kAligned : store == kvx::kStoreCached ? kvx::kFlatCached : kvx::kFlat;
 }
 
 // Shared argument checks of the launch calls; fills the kernel arguments.
