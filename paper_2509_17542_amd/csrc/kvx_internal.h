@@ -164,6 +164,8 @@ struct ItemsArgs {
     int32_t lens[kNoAllocRequests];   // tokens per request
     int32_t num_requests;
     int32_t block_size;               // destination page size
+    int32_t num_items;                // items of the table
+    int32_t pad;
     int64_t src_elems_per_token;      // elements of one token in a source shard (2 x layers x Hs x D)
     Item* items;                      // the table to write
 };

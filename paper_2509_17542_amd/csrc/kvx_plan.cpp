@@ -843,6 +843,7 @@ kvx_status kvx_repack_noalloc(const kvx_desc* desc, const void* const* shards, v
         for (int r = 0; r < d.num_requests; ++r) ia.lens[r] = d.seq_lens[r];
         ia.num_requests = d.num_requests;
         ia.block_size = d.block_size;
+        ia.num_items = int32_t(items);
         ia.src_elems_per_token = 2 * int64_t(src_layers_of(d)) * s.hs * d.head_dim;
         ia.items = table;
         e = kvx::build_items(ia, stream);
