@@ -182,17 +182,20 @@ def _check(status: int) -> None:
         raise KvxError(status, kvx_last_error())
 
 
+_Tensor = torch.Tensor
+
+
 def _addr(x) -> int | None:
     """Device (or host) address of a tensor, an int, or None."""
-    if x is None:
-        return None
-    if isinstance(x, torch.Tensor):
+    if isinstance(x, _Tensor):
         return x.data_ptr()
-    return int(x)
+    return None if x is None else int(x)
 
 
 def _stream(stream) -> int | None:
     if stream is None:
+        if torch.cuda.is_initialized():  # the raw handle, without a Stream object (2 us)
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
@@ -218,6 +221,13 @@ class Plan:
         info = kvx_plan_info()
         _check(_lib.kvx_plan_info_get(self, ctypes.byref(info)))
         self.touches = info.num_items > 0   # launches read or write anything
+        # plain integers for the launch calls
+        self.src_tp = self.sizes.src_tp
+        self.wire_bytes = self.sizes.wire_bytes
+        self.cache_bytes = self.sizes.cache_bytes
+        self.scale_bytes = self.sizes.scale_bytes
+        self.table_row = 4 * self.sizes.num_requests   # table bytes per column
+        self.shard_array = _vp * self.src_tp
 
     def __del__(self):
         h, self.handle = getattr(self, "handle", None), None
@@ -303,69 +313,73 @@ def kvx_plan_destroy(plan: Plan) -> None:
     _check(_lib.kvx_plan_destroy(h))
 
 
-def _need(x, nbytes: int, what: str, dtype=None) -> None:
+def _need(x, nbytes: int, what: str, dtype=None, index=None) -> None:
     """A torch tensor argument must be a contiguous device tensor (of `dtype`
     where given) holding at least the `nbytes` the plan's launches touch
     through it.  Bare addresses (ints) and None pass unchecked: the C calls
     check NULL and alignment, sizes are the caller's contract there."""
-    if not isinstance(x, torch.Tensor) or nbytes <= 0:
+    if nbytes <= 0 or not isinstance(x, _Tensor):
         return
+    if x.is_cuda and x.is_contiguous() and x.nbytes >= nbytes and \
+            (dtype is None or x.dtype == dtype):
+        return
+    if index is not None:
+        what = f"{what}[{index}]"
     if x.device.type != "cuda":
         raise ValueError(f"{what} must be a device tensor, not one on {x.device}")
     if not x.is_contiguous():
         raise ValueError(f"{what} must be contiguous")
     if dtype is not None and x.dtype != dtype:
         raise ValueError(f"{what} must be {dtype}, not {x.dtype}")
-    have = x.numel() * x.element_size()
-    if have < nbytes:
-        raise ValueError(f"{what} holds {have} bytes; the plan touches {nbytes}")
+    raise ValueError(f"{what} holds {x.nbytes} bytes; the plan touches {nbytes}")
 
 
 def _shard_array(plan: Plan, shards):
     """The host array of src_tp shard addresses, each read shard checked."""
     shards = list(shards)
-    if len(shards) < plan.sizes.src_tp:
-        raise ValueError(f"{len(shards)} source shards given; the plan has src_tp = "
-                         f"{plan.sizes.src_tp}")
-    arr = (_vp * max(len(shards), 1))()
+    n = plan.src_tp
+    if len(shards) < n:
+        raise ValueError(f"{len(shards)} source shards given; the plan has src_tp = {n}")
+    arr = plan.shard_array() if len(shards) == n else (_vp * len(shards))()
     for j, s in enumerate(shards):
-        if j < plan.sizes.src_tp:
-            _need(s, plan.shard_bytes[j], f"src_shards[{j}]")
+        if j < n:
+            _need(s, plan.shard_bytes[j], "src_shards", index=j)
         arr[j] = _addr(s)
     return arr
 
 
 def _table_bytes(plan: Plan, stride: int) -> int:
     """int32 bytes of a [num_requests][stride] block table, if launches read it."""
-    return 4 * plan.sizes.num_requests * max(int(stride), 0) if plan.touches else 0
+    return plan.table_row * max(int(stride), 0) if plan.touches else 0
 
 
 def _need_pool(plan: Plan, cache, scales, block_table, bt_stride: int) -> None:
     if not plan.touches:
         return
-    _need(cache, plan.sizes.cache_bytes, "cache")
-    _need(scales, plan.sizes.scale_bytes, "scales", torch.float32)
-    _need(block_table, _table_bytes(plan, bt_stride), "block_table", torch.int32)
+    _need(cache, plan.cache_bytes, "cache")
+    if scales is not None:
+        _need(scales, plan.scale_bytes, "scales", torch.float32)
+    _need(block_table, plan.table_row * max(int(bt_stride), 0), "block_table", torch.int32)
 
 
 def kvx_pack(plan: Plan, src_shards, wire, stream=None) -> None:
     if plan.touches:
-        _need(wire, plan.sizes.wire_bytes, "wire")
-    _check(_lib.kvx_pack(plan, _shard_array(plan, src_shards), _addr(wire), _stream(stream)))
+        _need(wire, plan.wire_bytes, "wire")
+    _check(_lib.kvx_pack(plan.handle, _shard_array(plan, src_shards), _addr(wire), _stream(stream)))
 
 
 def kvx_unpack(plan: Plan, wire, cache, scales, block_table, bt_stride: int, stream=None) -> None:
     if plan.touches:
-        _need(wire, plan.sizes.wire_bytes, "wire")
+        _need(wire, plan.wire_bytes, "wire")
     _need_pool(plan, cache, scales, block_table, bt_stride)
-    _check(_lib.kvx_unpack(plan, _addr(wire), _addr(cache), _addr(scales), _addr(block_table),
+    _check(_lib.kvx_unpack(plan.handle, _addr(wire), _addr(cache), _addr(scales), _addr(block_table),
                            bt_stride, _stream(stream)))
 
 
 def kvx_repack(plan: Plan, src_shards, cache, scales, block_table, bt_stride: int,
                stream=None) -> None:
     _need_pool(plan, cache, scales, block_table, bt_stride)
-    _check(_lib.kvx_repack(plan, _shard_array(plan, src_shards), _addr(cache), _addr(scales),
+    _check(_lib.kvx_repack(plan.handle, _shard_array(plan, src_shards), _addr(cache), _addr(scales),
                            _addr(block_table), bt_stride, _stream(stream)))
 
 
@@ -375,8 +389,8 @@ def kvx_repack_noalloc(desc: kvx_desc, src_shards, cache, scales, block_table, b
     its work-item table in a static device array).  Tensor arguments are
     checked against the sizes the descriptor implies: every shard given must
     hold one shard's bytes, whether the decode rank reads it or not."""
-    lens = [desc.seq_lens[r] for r in range(desc.num_requests)]
-    if sum(lens) > 0:
+    tokens = sum(desc.seq_lens[:desc.num_requests]) if desc.num_requests > 0 else 0
+    if tokens > 0:
         H, D = desc.num_kv_heads, desc.head_dim
         hs = H // desc.src_tp if 0 < desc.src_tp <= H else 1
         hd = H // desc.dst_tp if 0 < desc.dst_tp <= H else 1
@@ -390,7 +404,8 @@ def kvx_repack_noalloc(desc: kvx_desc, src_shards, cache, scales, block_table, b
         _need(block_table, 4 * desc.num_requests * max(int(bt_stride), 0), "block_table",
               torch.int32)
         for j, sh in enumerate(src_shards):
-            _need(sh, 2 * src_layers * sum(lens) * hs * D * 2, f"src_shards[{j}]")
+            if sh is not None:
+                _need(sh, 2 * src_layers * tokens * hs * D * 2, "src_shards", index=j)
     arr = (_vp * max(len(src_shards), 1))()
     for j, sh in enumerate(src_shards):
         arr[j] = _addr(sh)
@@ -401,9 +416,9 @@ def kvx_repack_noalloc(desc: kvx_desc, src_shards, cache, scales, block_table, b
 def kvx_pack_paged(plan: Plan, src_shards, src_block_table, src_bt_stride: int, wire,
                    stream=None) -> None:
     if plan.touches:
-        _need(wire, plan.sizes.wire_bytes, "wire")
+        _need(wire, plan.wire_bytes, "wire")
     _need(src_block_table, _table_bytes(plan, src_bt_stride), "src_block_table", torch.int32)
-    _check(_lib.kvx_pack_paged(plan, _shard_array(plan, src_shards), _addr(src_block_table),
+    _check(_lib.kvx_pack_paged(plan.handle, _shard_array(plan, src_shards), _addr(src_block_table),
                                src_bt_stride, _addr(wire), _stream(stream)))
 
 
@@ -411,7 +426,7 @@ def kvx_repack_paged(plan: Plan, src_shards, src_block_table, src_bt_stride: int
                      block_table, bt_stride: int, stream=None) -> None:
     _need_pool(plan, cache, scales, block_table, bt_stride)
     _need(src_block_table, _table_bytes(plan, src_bt_stride), "src_block_table", torch.int32)
-    _check(_lib.kvx_repack_paged(plan, _shard_array(plan, src_shards), _addr(src_block_table),
+    _check(_lib.kvx_repack_paged(plan.handle, _shard_array(plan, src_shards), _addr(src_block_table),
                                  src_bt_stride, _addr(cache), _addr(scales), _addr(block_table),
                                  bt_stride, _stream(stream)))
 

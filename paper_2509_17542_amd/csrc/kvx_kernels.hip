@@ -914,10 +914,11 @@ int go_conv(int conv, const KArgs& a, void* stream)
 // Workgroup g writes items 256 g .. 256 g + 255, one per thread.  Each takes
 // the prefix sums of the requests' pages and tokens by itself (a scan over the
 // at most 256 requests, one per thread, in LDS), then the request whose pages
-// cover its item is the first one whose pages end behind it.  The source offset of a request is its preceding tokens times
-// the elements of one token.  Latency-bound; against one workgroup with a serial
-// sum: 64 requests, 1100 pages 8.0 -> 4.8 us, and whole calls of 256 requests
-// with 33000 pages 218 -> 119 us.
+// cover its item is the first one whose pages end behind it.  The source
+// offset of a request is its preceding tokens times the elements of one token.
+// Latency-bound; against one workgroup with a serial sum: 64 requests, 1100
+// pages 8.0 -> 4.8 us, and whole calls of 256 requests with 33000 pages 218 ->
+// 119 us.
 __global__ void __launch_bounds__(kThreads) kvx_items_kernel(const ItemsArgs a)
 {
     static_assert(kNoAllocRequests <= kThreads, "one request per thread");
