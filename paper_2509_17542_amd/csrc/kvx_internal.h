@@ -86,8 +86,7 @@ enum Form : int { kAligned = 0, kFlat = 1, kFlatCached = 2 };
 
 // Kernel arguments (passed by value through the kernel-argument segment).  A
 // kernel reads the groups that its form needs whole, at its start, so that one
-// wait covers them all: Args, then Args2 (head-major, flat and 8-bit forms)
-// and ArgsPaged; a launch with one head segment does not read seg[].
+// wait covers them all: Args and, of paged sources, ArgsPaged; a launch with one head segment does not read seg[].
 struct Args {
     uint32_t units;                   // work units: planes x pages x segments x parts
     uint32_t units_per_xcd;           // grid / kXcds
@@ -121,9 +120,8 @@ struct Args {
     int64_t plane_scales;             // cache scales per plane
 };
 
-struct Args2 {
-    FastDiv div_bs;
-    // flat launches: the rows of a plane's pages packed into workgroups
+struct ArgsFlat {                     // flat launches: the rows of a plane's pages
+                                      // packed into workgroups
     uint32_t row_lanes;               // lanes per row: cpr, or the power of two above it
     uint32_t page_rows;               // rows of a page in its widest segment
     FastDiv div_row_lanes, div_page_rows;
@@ -141,13 +139,13 @@ struct ArgsPaged {                    // paged sources: the prefill side's pages
 
 struct KArgs {
     Args a;
-    Args2 b;
+    ArgsFlat b;
     ArgsPaged p;
     int32_t form;                     // Form: which kernel (read by the host)
     int32_t pad;
     Segment seg[kMaxReadShards];      // pack/repack: the head segments; unpack: one, all heads
 };
-static_assert(sizeof(Args) == 192 && sizeof(Args2) == 32 && sizeof(ArgsPaged) == 40,
+static_assert(sizeof(Args) == 192 && sizeof(ArgsFlat) == 24 && sizeof(ArgsPaged) == 40,
               "the kernels read the argument groups as whole dwords");
 
 // Launch one conversion over the arguments' work units; returns a hipError_t value.

@@ -592,9 +592,10 @@ __device__ __forceinline__ void convert_part(const KArgs& k)
     // unconditionally (lanes without a row read the buffer's first vector), so
     // the lookups, the row loads and the paged source's page lookup overlap
     // instead of following one another.  Measured faster for repacks from
-    // paged sources (+16%) and 16-bit token-major rows (+2%); the head-major
-    // and 8-bit paths measure 2-4% faster with the row load inside the
-    // branch, and the pack from paged sources the same either way.
+    // paged sources (+16%) and 16-bit token-major rows (+2%); the head-major,
+    // 8-bit and paged pack paths measure the same either way where rows fill
+    // their lanes, and up to 8% slower early where they do not (80 x e4m3fn,
+    // head-major: 193 against 208 us).
     constexpr bool kEarly =
         FLAT || (ORDER == KVX_PAGED && MODE != kPack) ||
         (ORDER == KVX_THD && (CONV == kCopy16 || CONV == kF16Bf16 || CONV == kBf16F16));
@@ -604,9 +605,8 @@ __device__ __forceinline__ void convert_part(const KArgs& k)
     // where they are used (all at once: repack of 5-token pages from a paged
     // source 389 -> 410 us).
     const Args a = FLAT ? k.a : read_args(k.a);
-    Args2 f{};
+    ArgsFlat f{};
     if constexpr (FLAT) f = k.b;
-    else if constexpr (ORDER == KVX_HTD && MODE != kUnpack) f = read_args(k.b);
     ArgsPaged g{};
     if constexpr (ORDER == KVX_PAGED && MODE != kUnpack) g = FLAT ? k.p : read_args(k.p);
 
@@ -673,19 +673,15 @@ __device__ __forceinline__ void convert_part(const KArgs& k)
         }
     }
 
-    int s, ii;  // token within the page, head within the segment
-    bool ok;
-    if constexpr (ORDER == KVX_HTD && MODE != kUnpack) {
-        // head-major rows: consecutive lane groups read consecutive tokens of one
-        // head, contiguous in a [head][token][dim] source
-        ii = int(fdiv(uint32_t(r), f.div_bs));
-        s = r - ii * a.block_size;
-        ok = live && sub < a.cpr && ii < seg.n && s < min(a.block_size, T - t0);
-    } else {
-        s = int(fdiv(uint32_t(r), seg.div_n));
-        ii = r - s * seg.n;
-        ok = live && sub < a.cpr && r < seg_rows;
-    }
+    // Rows go to the lanes token by token, as the destination holds them, from
+    // a head-major source as well: rows of one head that share a line are then
+    // read by different lane groups, out of the L2, and the stores leave whole.  In
+    // the source's order (consecutive lanes on consecutive tokens of one head),
+    // 4 heads x 80 fp16 -> bf16 took 273 us against 236, x 112 342 against
+    // 311, x 64 into e4m3fn 171 against 143, x 128 335 against 334.
+    const int s = int(fdiv(uint32_t(r), seg.div_n));  // token within the page
+    const int ii = r - s * seg.n;                     // head within the segment
+    bool ok = live && sub < a.cpr && r < seg_rows;
     const int row = s * a.hd + seg.i0 + ii;                 // row within the page
 
     // source address of this lane's row (meaningful where ok)

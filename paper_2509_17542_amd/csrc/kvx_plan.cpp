@@ -484,12 +484,12 @@ struct OneRequest {
 
 // How the launch writes its destination rows, by the bytes that one store
 // instruction of a wave covers in one piece: the rows that its lanes hold where
-// those follow one another in the destination, else those of one token's heads,
-// or one row; half a row where a dequantising lane writes each half by itself.
+// those follow one another in the destination, else those of one token's heads
+// from one shard; half a row where a dequantising lane writes each half by itself.
 //  - Pieces that are not whole 64-byte sectors leave parts of a sector to
-//    another instruction: the L2 merges them (kStoreCached).  160-byte rows
-//    of a head-major source 295 -> 273 us, 112-byte half rows 341 -> 270, 160-
-//    byte rows at 320 72 -> 58; written through they take 418, 634 and 90.
+//    another instruction: the L2 merges them (kStoreCached).  112-byte half
+//    rows 341 -> 270 us, 160-byte rows at 320 72 -> 58; written through they
+//    take 634 and 90.
 //    Long pieces (512 bytes on) meet at few of their sectors and stream.
 //  - Whole sectors stream past the caches.  Written through the L2 as well
 //    they reach memory in the order of the launch: packs 3% faster (14266
@@ -504,13 +504,11 @@ int store_policy(const kvx_desc& d, const kvx::Shape& s, int mode, const kvx::KA
 {
     const kvx::Args& a = k.a;
     const bool halves = s.dequant && mode != kvx::kPack;
-    // (a head-major source's rows of one head: the next token's follows where it is the only one)
-    const bool head_major = mode != kvx::kUnpack && d.src_order == KVX_HTD && s.hd > 1;
     int64_t piece = a.row_dst_bytes;
     if (halves) piece /= 2;
-    else if (a.num_segs == 1 && !head_major)
+    else if (a.num_segs == 1)
         piece = flat_row_lanes == s.cpr ? 1024 : (64 >> s.lg_lpr) * piece;
-    else if (!head_major) {
+    else {
         const int64_t row = piece;
         piece = a.seg0.n * row;
         for (uint32_t j = 1; j < a.num_segs; ++j)  // the smallest, a broken sector first
@@ -535,7 +533,7 @@ void fill_args(const kvx_desc& d, const kvx::Shape& s, int mode, uint32_t num_it
                float* scales, const int32_t* bt, int32_t bt_stride, int layer_shift, kvx::KArgs& k)
 {
     kvx::Args& a = k.a;
-    kvx::Args2& f = k.b;
+    kvx::ArgsFlat& f = k.b;
     a.dst = dst;
     a.dscale = scales;
     a.items = items;
@@ -572,8 +570,8 @@ void fill_args(const kvx_desc& d, const kvx::Shape& s, int mode, uint32_t num_it
     //    head_dim 80 510 -> 422 us, 96 531 -> 507, but 112 591 -> 592.  A
     //    paged source's repack, with a second lookup per lane, at 5/8 (80:
     //    287 -> 254 us), its pack not (80: 246 -> 249, 96: 258 -> 289).  Not
-    //    from head-major sources (80: 575 -> 595) nor for dequantisation (80:
-    //    149 -> 185); quantising rows reduce over aligned lanes.
+    //    for dequantisation (80: 149 -> 185); quantising rows reduce over
+    //    aligned lanes.
     //  - Otherwise a launch is flat when a page's rows fill at most 3/4 of its
     //    workgroups (8-bit types, bound by the vector ALUs as well: 5/8).
     //    6-token pages of 4 heads x 128 (3/4) 414 -> 392 us, but 10-token
@@ -588,7 +586,6 @@ void fill_args(const kvx_desc& d, const kvx::Shape& s, int mode, uint32_t num_it
     const int64_t lpr = int64_t(1) << s.lg_lpr;
     int chunk_eighths = 6;  // of its lanes that a row packed chunk by chunk may fill
     if (is_fp8(d.dst_dtype)) chunk_eighths = 0;
-    else if (mode != kvx::kUnpack && d.src_order == KVX_HTD && max_n > 1) chunk_eighths = 0;
     else if (mode != kvx::kUnpack && d.src_order == KVX_PAGED) chunk_eighths = mode == kvx::kPack ? 0 : 5;
     const bool by_chunk = s.cpr * 8 <= lpr * chunk_eighths;
     f.row_lanes = uint32_t(by_chunk ? s.cpr : lpr);
@@ -607,7 +604,6 @@ void fill_args(const kvx_desc& d, const kvx::Shape& s, int mode, uint32_t num_it
     a.div_parts = kvx::make_fastdiv(a.parts);
     a.div_segs = kvx::make_fastdiv(a.num_segs);
     a.div_items = kvx::make_fastdiv(a.num_items);
-    f.div_bs = kvx::make_fastdiv(uint32_t(d.block_size));
     a.num_blocks = d.num_blocks;
     a.plane_bytes = d.num_blocks * d.block_size * int64_t(s.hd) * d.head_dim * s.esz_cache;
     a.plane_scales = d.num_blocks * d.block_size * int64_t(s.hd);
