@@ -294,8 +294,9 @@ kvx_status kvx_repack_paged(const kvx_plan_t *plan, const void *const *src_shard
  * (token- or head-major sources), with no plan: the work-item table that
  * kvx_plan would allocate lives in a static device array of the library (one
  * per device, 65536 entries of 40 bytes), written by a small kernel on
- * hip_stream before the repack kernel.  Nothing is allocated on the host
- * heap or the device; the call enqueues two kernels and returns.
+ * hip_stream before the repack kernel; tokens in a single request need no
+ * table.  Nothing is allocated on the host heap or the device; the call
+ * enqueues one or two kernels and returns.
  *   desc:        as kvx_plan (copied; seq_lens read during the call only);
  *                at most 256 requests and 65536 destination pages in all
  *                (sum of ceil(T_r / block_size)), else KVX_EUNSUPPORTED.

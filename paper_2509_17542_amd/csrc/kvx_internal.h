@@ -84,9 +84,10 @@ enum Store : int { kStoreStream = 0, kStoreThrough = 1, kStoreCached = 2 };
 // into workgroups, written with kStoreStream or kStoreCached.
 enum Form : int { kAligned = 0, kFlat = 1, kFlatCached = 2 };
 
-// Kernel arguments (passed by value through the kernel-argument segment).  A
-// kernel reads the groups that its form needs whole, at its start, so that one
-// wait covers them all: Args and, of paged sources, ArgsPaged; a launch with one head segment does not read seg[].
+// Kernel arguments (passed by value through the kernel-argument segment).  The
+// page-aligned form reads the groups that it needs whole, at its start, so that
+// one wait covers them all: Args and, for paged sources, ArgsPaged; a launch
+// with one head segment does not read seg[].
 struct Args {
     uint32_t units;                   // work units: planes x pages x segments x parts
     uint32_t units_per_xcd;           // grid / kXcds
@@ -143,7 +144,7 @@ struct KArgs {
     ArgsPaged p;
     int32_t form;                     // Form: which kernel (read by the host)
     int32_t pad;
-    Segment seg[kMaxReadShards];      // pack/repack: the head segments; unpack: one, all heads
+    Segment seg[kMaxReadShards];      // the head segments, where there is more than one
 };
 static_assert(sizeof(Args) == 192 && sizeof(ArgsFlat) == 24 && sizeof(ArgsPaged) == 40,
               "the kernels read the argument groups as whole dwords");

@@ -26,8 +26,9 @@
 // the source block table.  Rows of one token are contiguous in a source page,
 // as in a token-major source, so the unit and row order are the same.
 //
-// Row loads and stores are non-temporal: every row is read once and the
-// destination is not read again by this launch.
+// Row loads are non-temporal: every row is read once.  Stores are non-temporal,
+// written through or kept in the L2, by what a store instruction covers
+// (store_rows; the planner's rule has the sizes).
 //
 // Flat launches.  The units above give every page whole workgroups, which is
 // what makes the page's addresses scalar; where that leaves many lanes idle
