@@ -486,11 +486,22 @@ struct OneRequest {
 // instruction of a wave covers in one piece: the rows that its lanes hold where
 // those follow one another in the destination, else those of one token's heads
 // from one shard; half a row where a dequantising lane writes each half by itself.
+// A piece of the cache ends with its page, which the next page of the launch
+// does not follow in memory.
 //  - Pieces that are not whole 64-byte sectors leave parts of a sector to
 //    another instruction: the L2 merges them (kStoreCached).  112-byte half
 //    rows 341 -> 270 us, 160-byte rows at 320 72 -> 58; written through they
 //    take 634 and 90.
-//    Long pieces (512 bytes on) meet at few of their sectors and stream.
+//    Pieces of 512 bytes on meet at few of their sectors and stream: 896-byte
+//    ones of a pack 107 us against 116 cached, in 300 MB of 2464-byte pages
+//    137 against 147.  The line is rough: two shards' 672- and 1568-byte pieces
+//    merged in 150 MB of cache take 69 and 59 us against 58 and 51 cached.
+//  - Broken sectors at the ends of short pages, whose other part belongs to
+//    another page, meet in the memory-side cache (256 MB) instead: kept in the
+//    L2 where the launch fits that, streamed where it does not, but for the
+//    shortest pages.  One-token pages of 160 bytes, streamed and cached: 137 and
+//    75 us in 200 MB, 279 and 261 in 400 MB; 176 bytes 235 and 166, 477 and
+//    477; 224 bytes 115 and 80, 239 and 247; 480 bytes 93 and 70, 192 and 216.
 //  - Whole sectors stream past the caches.  Written through the L2 as well
 //    they reach memory in the order of the launch: packs 3% faster (14266
 //    tokens, 128 KB each: 580 -> 562 us; 1900 tokens 78.2 -> 75.4), 64 KB pages
@@ -518,11 +529,16 @@ int store_policy(const kvx_desc& d, const kvx::Shape& s, int mode, const kvx::KA
     // the runs of rows that the pieces are cut from start in whole sectors too:
     // the pages of the cache, the tokens of the transfer tensor
     const int64_t run = int64_t(s.hd) * a.row_dst_bytes * (mode == kvx::kPack ? 1 : d.block_size);
-    if (piece % 64 || run % 64) return piece < 512 ? kvx::kStoreCached : kvx::kStoreStream;
-    if (flat_row_lanes || piece < (halves ? 192 : 128)) return kvx::kStoreStream;
-    if (mode == kvx::kPack) return kvx::kStoreThrough;
     const int64_t bytes = num_items * d.block_size * a.planes * s.hd * int64_t(a.row_dst_bytes);
-    return bytes > (int64_t(256) << 20) ? kvx::kStoreThrough : kvx::kStoreStream;
+    const bool large = bytes > (int64_t(256) << 20);
+    const bool short_page = mode != kvx::kPack && run < piece;
+    if (short_page) piece = run;
+    if (piece % 64 || run % 64) {
+        const bool cached = short_page && large ? piece <= 160 : piece < 512;
+        return cached ? kvx::kStoreCached : kvx::kStoreStream;
+    }
+    if (flat_row_lanes || piece < (halves ? 192 : 128)) return kvx::kStoreStream;
+    return mode == kvx::kPack || large ? kvx::kStoreThrough : kvx::kStoreStream;
 }
 
 // The kernel arguments every launch mode shares, from the descriptor, its

@@ -1,0 +1,127 @@
+"""What the planner's rules choose for a launch, checked on the CPU: the
+planner and the launch calls run with the HIP runtime and the kernels replaced
+(tests/launch_probe.cpp), so the arguments of every launch can be read."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from conftest import ROOT
+
+import paper_2509_17542_amd as K
+
+CSRC = os.path.join(ROOT, "paper_2509_17542_amd", "csrc")
+STREAM, THROUGH, CACHED = 0, 1, 2                # kvx_internal.h, Store
+ALIGNED, FLAT, FLAT_CACHED = 0, 1, 2             # kvx_internal.h, Form
+MODES = ("pack", "unpack", "repack")
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None or
+                                not os.path.exists("/opt/rocm/include/hip"),
+                                reason="needs g++ and the HIP headers")
+
+
+@pytest.fixture(scope="module")
+def probe(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("probe") / "probe.so")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wl,-Bsymbolic",
+                    "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-I",
+                    "/opt/rocm/include", os.path.join(ROOT, "tests", "launch_probe.cpp"),
+                    os.path.join(CSRC, "kvx_plan.cpp"), "-o", so], check=True, capture_output=True)
+    lib = ctypes.CDLL(so)
+    lib.probe_walk.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32, ctypes.c_int,
+                               ctypes.c_void_p]
+    lib.kvx_last_error.restype = ctypes.c_char_p
+    for name in ("kvx_plan_info_get", "kvx_plan_destroy", "kvx_pack", "kvx_pack_paged", "kvx_unpack",
+                 "kvx_repack", "kvx_repack_paged"):
+        getattr(lib, name).argtypes = getattr(K._lib, name).argtypes
+    return lib
+
+
+class Launch:
+    """One plan in the probe; `launch(mode)` makes the call on made-up aligned
+    addresses (nothing reads them) and returns its arguments."""
+    BT, STRIDE, SBT = 0x40000, 1 << 20, 0x50000
+
+    def __init__(self, lib, desc):
+        self.lib, self.desc, self.plan = lib, desc, ctypes.c_void_p()
+        self.ok(lib.kvx_plan(ctypes.byref(desc), ctypes.byref(self.plan)))
+        self.info = K.kvx_plan_info()
+        self.ok(lib.kvx_plan_info_get(self.plan, ctypes.byref(self.info)))
+
+    def ok(self, status):
+        assert status == K.OK, self.lib.kvx_last_error()
+
+    def launch(self, mode):
+        d, lib = self.desc, self.lib
+        shards = (ctypes.c_void_p * d.src_tp)(*[0x10000] * d.src_tp)
+        cache_t = d.cache_dtype or d.dst_dtype
+        cache = (0x20000, 0x30000 if cache_t in (K.E4M3FN, K.E5M2) else None, self.BT, self.STRIDE)
+        sbt = (self.SBT, self.STRIDE) if d.src_order == K.PAGED else ()
+        paged = "_paged" if sbt else ""
+        if mode == "pack":
+            self.ok(getattr(lib, "kvx_pack" + paged)(self.plan, shards, *sbt, 0x60000, None))
+        elif mode == "unpack":
+            self.ok(lib.kvx_unpack(self.plan, 0x60000, *cache, None))
+        else:
+            self.ok(getattr(lib, "kvx_repack" + paged)(self.plan, shards, *sbt, *cache, None))
+        v = (ctypes.c_int64 * 9)()
+        assert lib.probe_launch(v) == 9
+        names = ("launches", "form", "store", "units", "planes", "items", "segs", "page_rows", "cpr")
+        return dict(zip(names, v))
+
+    def close(self):
+        self.lib.kvx_plan_destroy(self.plan)
+
+
+def one_segment(heads, dim, page, wire=K.BF16, tokens=4096, cache=0):
+    """One shard to one rank: `heads` heads of `dim`, pages of `page` tokens."""
+    return K.make_desc(2, heads, dim, 1, 1, 0, K.BF16, wire, K.THD, page, 1 << 16, [tokens],
+                       cache_dtype=cache)
+
+
+# A flat launch's lanes follow one another across pages, but what they write
+# in one piece ends with the page: broken sectors of short pages are left to
+# the L2, whatever the rows of a wave add up to.
+SHORT_PAGES = [(1, 80, 1, K.BF16), (1, 112, 1, K.BF16), (3, 80, 1, K.BF16), (1, 16, 3, K.BF16),
+               (1, 80, 3, K.BF16), (1, 80, 1, K.E4M3FN), (1, 112, 1, K.E4M3FN),
+               (1, 80, 5, K.E4M3FN), (1, 16, 5, K.E4M3FN)]
+
+
+@pytest.mark.parametrize("mode", ["unpack", "repack"])
+@pytest.mark.parametrize("heads,dim,page,wire", SHORT_PAGES)
+def test_short_pages_of_broken_sectors_are_cached(probe, heads, dim, page, wire, mode):
+    run = heads * page * dim * (1 if wire == K.E4M3FN else 2)
+    assert run % 64 and run < 512
+    p = Launch(probe, one_segment(heads, dim, page, wire))
+    a = p.launch(mode)
+    p.close()
+    assert (a["form"], a["store"]) == (FLAT_CACHED, CACHED)
+
+
+@pytest.mark.parametrize("heads,dim,page,store", [(1, 80, 1, CACHED), (1, 88, 1, STREAM),
+                                                  (1, 112, 1, STREAM), (3, 80, 1, STREAM)])
+def test_short_pages_above_the_memory_side_cache(probe, heads, dim, page, store):
+    """160, 176, 224 and 480 bytes, just above 256 MB of them."""
+    tokens = (256 << 20) // (2 * 2 * heads * dim * 2) + 1
+    p = Launch(probe, K.make_desc(2, heads, dim, 1, 1, 0, K.BF16, K.BF16, K.THD, page, 1 << 20,
+                                  [tokens]))
+    assert p.launch("repack")["store"] == store
+    p.close()
+    p = Launch(probe, K.make_desc(2, heads, dim, 1, 1, 0, K.BF16, K.BF16, K.THD, page, 1 << 20,
+                                  [tokens - 1]))
+    assert p.launch("repack")["store"] == CACHED
+    p.close()
+
+
+@pytest.mark.parametrize("heads,dim,page,wire,form,store", [
+    (1, 128, 1, K.BF16, FLAT, STREAM),          # 256-byte pages: whole sectors
+    (2, 96, 1, K.BF16, FLAT, STREAM),           # 384
+    (1, 80, 5, K.BF16, FLAT, STREAM),           # 800: broken, 512 bytes and more
+    (8, 128, 16, K.BF16, ALIGNED, STREAM)])     # 32 KB pages, a cache below 256 MB
+def test_other_pages_stream(probe, heads, dim, page, wire, form, store):
+    p = Launch(probe, one_segment(heads, dim, page, wire))
+    a = p.launch("repack")
+    p.close()
+    assert (a["form"], a["store"]) == (form, store)
