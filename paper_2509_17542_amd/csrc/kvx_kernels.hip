@@ -807,11 +807,19 @@ __device__ __forceinline__ void convert_part(const KArgs& k)
             store_rows<2, FORM>({drow + sub * 16, drow + (sub + a.cpr) * 16}, {out, out2}, a.store);
         else
             store_rows<1, FORM>({drow + sub * 16}, {out}, a.store);
-        if constexpr (kScales && (FLAT || !kFp8))  // the 8-bit unpack: the scale it loaded
+        // The flat quantisers' row scales, from lanes that may lie in several
+        // pages, are pieces of sectors that the L2 merges: ordinary stores.
+        // Against non-temporal ones, one head of 128 e4m3fn codes: one-token
+        // pages 121 -> 93 us, five-token pages 119 -> 108, 16-token pages 107.2
+        // -> 105.7.  The 8-bit unpack stores the scale it loaded non-temporally.
+        if constexpr (kFp8 && FLAT) {
+            if (sub == 0) *(global_ptr<float>)(sbase + row) = sc;
+        } else if constexpr (kScales && !kFp8) {
             if (sub == 0) __builtin_nontemporal_store(sc, (global_ptr<float>)(sbase + row));
+        }
     }
     if constexpr (kFp8 && !FLAT) {
-        // The quantising launches' 4-byte row scales go out through LDS: lane
+        // The page-aligned quantisers' 4-byte row scales go out through LDS: lane
         // 0 of each row leaves its scale and destination slot there, and after
         // the barrier the first lanes of wave 0 store them all, so a
         // workgroup's 32 or so consecutive scales leave as one store
