@@ -192,10 +192,17 @@ def _addr(x) -> int | None:
     return None if x is None else int(x)
 
 
+# the current stream's raw handle, without a Stream object (2 us): private calls
+# of torch, so the public ones serve where a version lacks them
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+_has_raw = _raw_stream is not None and _raw_device is not None
+
+
 def _stream(stream) -> int | None:
     if stream is None:
-        if torch.cuda.is_initialized():  # the raw handle, without a Stream object (2 us)
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _has_raw and torch.cuda.is_initialized():
+            return _raw_stream(_raw_device())
         return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
