@@ -32,7 +32,7 @@ ONES = (1,) * 40
 FLAT = {w.name: w for w in [
     _w(QWEN, "token_pages_hd80_tp2to3", (1, 37, 0, 130), src_order="thd", heads=6, head_dim=80,
        src_tp=2, dst_tp=3, dst_rank=1, block_size=1),
-    _w(L8B, "one_token_requests", ONES, heads=2, head_dim=64, block_size=16),
+    _w(L8B, "one_token_requests", ONES, heads=2, head_dim=64, block_size=8),
     _w(L8B, "unequal_segments", (23, 1, 40), heads=12, head_dim=96, src_tp=3, dst_tp=2,
        block_size=5),
     _w(L8B, "chunks33_bf16", (9, 30), heads=2, head_dim=264, block_size=3),
@@ -41,9 +41,9 @@ FLAT = {w.name: w for w in [
     _w(FP8, "one_lane_rows_e4m3", (1, 65, 200), heads=1, head_dim=16, block_size=1),
     _w(FP8, "rows21_per_wave_e5m2", (40, 22), heads=4, head_dim=48, dst_dtype="e5m2",
        src_order="htd", block_size=3),
-    _w(FP8, "one_row_per_wave_e4m3", (17, 6), heads=2, head_dim=528, block_size=5),
+    _w(FP8, "one_row_per_wave_e4m3", (17, 6), heads=2, head_dim=528, block_size=1),
     _w(FP8, "chunks62_e4m3_bf16", (11, 4), heads=1, head_dim=992, cache_dtype="bf16",
-       block_size=4),
+       block_size=2),
     _w(P8B, "paged3_hd112_e5m2_bf16", (50, 0, 7), heads=4, head_dim=112, dst_dtype="e5m2",
        cache_dtype="bf16", dst_tp=2, block_size=5, src_block_size=3),
     _w(P8B, "paged_one_head_bf16_fp16", (33, 90), heads=4, head_dim=64, dst_dtype="fp16",

@@ -9,6 +9,8 @@ import subprocess
 import pytest
 
 from conftest import ROOT
+from gpu_util import desc_for
+from test_gpu_flat import FLAT as FLAT_CASES
 
 import paper_2509_17542_amd as K
 
@@ -30,8 +32,6 @@ def probe(tmp_path_factory):
                     "/opt/rocm/include", os.path.join(ROOT, "tests", "launch_probe.cpp"),
                     os.path.join(CSRC, "kvx_plan.cpp"), "-o", so], check=True, capture_output=True)
     lib = ctypes.CDLL(so)
-    lib.probe_walk.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32, ctypes.c_int,
-                               ctypes.c_void_p]
     lib.kvx_last_error.restype = ctypes.c_char_p
     for name in ("kvx_plan_info_get", "kvx_plan_destroy", "kvx_pack", "kvx_pack_paged", "kvx_unpack",
                  "kvx_repack", "kvx_repack_paged"):
@@ -66,9 +66,9 @@ class Launch:
             self.ok(lib.kvx_unpack(self.plan, 0x60000, *cache, None))
         else:
             self.ok(getattr(lib, "kvx_repack" + paged)(self.plan, shards, *sbt, *cache, None))
-        v = (ctypes.c_int64 * 9)()
-        assert lib.probe_launch(v) == 9
-        names = ("launches", "form", "store", "units", "planes", "items", "segs", "page_rows", "cpr")
+        v = (ctypes.c_int64 * 8)()
+        assert lib.probe_launch(v) == 8
+        names = ("form", "store", "units", "planes", "items", "segs", "page_rows", "cpr")
         return dict(zip(names, v))
 
     def close(self):
@@ -125,3 +125,14 @@ def test_other_pages_stream(probe, heads, dim, page, wire, form, store):
     a = p.launch("repack")
     p.close()
     assert (a["form"], a["store"]) == (form, store)
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("name", list(FLAT_CASES))
+def test_flat_cases_are_flat(probe, name, mode):
+    """Every launch of tests/test_gpu_flat.py runs a flat kernel."""
+    w = FLAT_CASES[name]
+    p = Launch(probe, desc_for(w, w.lens_override))
+    a = p.launch(mode)
+    p.close()
+    assert a["form"] != ALIGNED
