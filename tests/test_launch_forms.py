@@ -6,8 +6,10 @@ import os
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 
+from cases import random_workloads
 from conftest import ROOT
 from gpu_util import desc_for
 from test_gpu_flat import FLAT as FLAT_CASES
@@ -32,6 +34,8 @@ def probe(tmp_path_factory):
                     "/opt/rocm/include", os.path.join(ROOT, "tests", "launch_probe.cpp"),
                     os.path.join(CSRC, "kvx_plan.cpp"), "-o", so], check=True, capture_output=True)
     lib = ctypes.CDLL(so)
+    lib.probe_walk.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32, ctypes.c_int,
+                               ctypes.c_void_p]
     lib.kvx_last_error.restype = ctypes.c_char_p
     for name in ("kvx_plan_info_get", "kvx_plan_destroy", "kvx_pack", "kvx_pack_paged", "kvx_unpack",
                  "kvx_repack", "kvx_repack_paged"):
@@ -136,3 +140,52 @@ def test_flat_cases_are_flat(probe, name, mode):
     a = p.launch(mode)
     p.close()
     assert a["form"] != ALIGNED
+
+
+RANDOM = {**FLAT_CASES, **random_workloads(31, 160)}
+
+
+@pytest.mark.parametrize("name", list(RANDOM))
+def test_every_row_has_one_lane(probe, name):
+    """Page-aligned or flat, each 16-byte chunk of each row of each page is
+    taken by exactly one lane, the rows of a quantising launch by aligned
+    lanes, and the only request's pages are those of the plan."""
+    w = RANDOM[name]
+    lens = w.lens_override
+    p = Launch(probe, desc_for(w, lens))
+    for mode in MODES if p.info.num_items else ():
+        a = p.launch(mode)
+        assert a["items"] == p.info.num_items
+        hits = np.zeros((a["planes"], a["items"], a["segs"], a["page_rows"], a["cpr"]), np.uint8)
+        assert probe.probe_walk(p.plan, p.BT if mode != "pack" else None, p.STRIDE,
+                                w.dst_dtype in ("e4m3fn", "e5m2"), hits.ctypes.data) == 0
+        want = np.zeros_like(hits)
+        item = 0
+        heads = segments(w) if mode != "unpack" else [w.hd]
+        assert len(heads) == a["segs"]
+        for t in lens:
+            for t0 in range(0, t, w.block_size):
+                for sg, n in enumerate(heads):
+                    want[:, item, sg, :min(w.block_size, t - t0) * n] = 1
+                item += 1
+        assert np.array_equal(hits, want), (mode, a)
+    p.close()
+
+
+def segments(w):
+    """Heads of each run of the decode rank's heads that lies in one shard."""
+    g0 = w.dst_rank * w.hd if w.dst_tp <= w.heads else w.dst_rank // (w.dst_tp // w.heads)
+    shard = [(g0 + i) // w.hs for i in range(w.hd)]
+    return [shard.count(j) for j in sorted(set(shard))]
+
+
+def test_random_launches_take_both_forms(probe):
+    forms = []
+    for name, w in RANDOM.items():
+        p = Launch(probe, desc_for(w, w.lens_override))
+        if p.info.num_items:
+            forms += [(p.launch(m)["form"], w.dst_dtype in ("e4m3fn", "e5m2")) for m in MODES]
+        p.close()
+    for form in (ALIGNED, FLAT, FLAT_CACHED):
+        for codes in (False, True):
+            assert forms.count((form, codes)) >= 10, (form, codes)
