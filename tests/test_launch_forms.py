@@ -13,6 +13,7 @@ from cases import random_workloads
 from conftest import ROOT
 from gpu_util import desc_for
 from test_gpu_flat import FLAT as FLAT_CASES
+import test_gpu_stores as stores
 
 import paper_2509_17542_amd as K
 
@@ -140,6 +141,19 @@ def test_flat_cases_are_flat(probe, name, mode):
     a = p.launch(mode)
     p.close()
     assert a["form"] != ALIGNED
+
+
+@pytest.mark.parametrize("src,wire,cache,dim", stores.TYPES)
+def test_store_cases_are_written_through(probe, src, wire, cache, dim):
+    """The launches of tests/test_gpu_stores.py: the whole cache is written
+    through, one layer of it streamed."""
+    for layers, store in ((stores.L, THROUGH), (1, STREAM)):
+        p = Launch(probe, K.make_desc(layers, stores.H, dim, 1, 1, 0, src, wire, K.THD, stores.BS,
+                                      2000, [stores.T], cache_dtype=0 if cache == wire else cache))
+        for mode in ("repack", "unpack"):
+            a = p.launch(mode)
+            assert (a["form"], a["store"]) == (ALIGNED, store)
+        p.close()
 
 
 RANDOM = {**FLAT_CASES, **random_workloads(31, 160)}
