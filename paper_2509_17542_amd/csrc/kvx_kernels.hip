@@ -801,6 +801,11 @@ __device__ __forceinline__ void convert_part(const KArgs& k)
         out = to_f16x8(v[0]);
     else
         out = v[0];
+    // The 8-bit unpack's scale is waited for together with its row: waited for
+    // at its own store, behind the row's, the wait covers that store as well
+    // (both are counted in vmcnt).  8 heads x 128 codes, 16-token pages: 2.9 GB
+    // into a pool of 69 GB 1049 -> 1010 us, 4.3 GB into 137 GB 1415 -> 1313.
+    if constexpr (kScales && !kFp8) __asm__ volatile("" : "+v"(sc));
     if (ok) {
         char* drow = dbase + int64_t(row) * a.row_dst_bytes;
         if constexpr (kHalves)
