@@ -812,12 +812,13 @@ __device__ __forceinline__ void convert_part(const KArgs& k)
             store_rows<2, FORM>({drow + sub * 16, drow + (sub + a.cpr) * 16}, {out, out2}, a.store);
         else
             store_rows<1, FORM>({drow + sub * 16}, {out}, a.store);
-        // The flat quantisers' row scales, from lanes that may lie in several
-        // pages, are pieces of sectors that the L2 merges: ordinary stores.
-        // Against non-temporal ones, one head of 128 e4m3fn codes: one-token
-        // pages 121 -> 93 us, five-token pages 119 -> 108, 16-token pages 107.2
-        // -> 105.7.  The 8-bit unpack stores the scale it loaded non-temporally.
-        if constexpr (kFp8 && FLAT) {
+        // A flat wave's row scales, from lanes that may lie in several pages,
+        // are pieces of sectors that the L2 merges: ordinary stores.  Against
+        // non-temporal ones, one head of 128 e4m3fn codes, repack and unpack:
+        // one-token pages 123 -> 94 and 100 -> 58 us, five-token pages 121 -> 109
+        // and 82 -> 70, 16-token pages 107.5 -> 106.3 and 69.7 -> 68.7.  The
+        // page-aligned 8-bit unpack stores its scales non-temporally.
+        if constexpr (kScales && FLAT) {
             if (sub == 0) *(global_ptr<float>)(sbase + row) = sc;
         } else if constexpr (kScales && !kFp8) {
             if (sub == 0) __builtin_nontemporal_store(sc, (global_ptr<float>)(sbase + row));

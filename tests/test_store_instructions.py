@@ -48,9 +48,14 @@ def _quantisers(kernels, *forms):
     return pick
 
 
-def test_quantisers_leave_their_scales_to_the_l2(kernels):
-    """A wave's 4-byte row scales are pieces of sectors: never streamed."""
-    for k, code in _quantisers(kernels, ALIGNED, FLAT, FLAT_CACHED).items():
+def test_scales_are_left_to_the_l2(kernels):
+    """A wave's 4-byte row scales are pieces of sectors: never streamed by the
+    quantisers and the flat unpack."""
+    pick = _quantisers(kernels, ALIGNED, FLAT, FLAT_CACHED)
+    pick.update({k: v for k, v in kernels.items()
+                 if k[:2] == ("unpack", COPY8) and k[3] in (FLAT, FLAT_CACHED)})
+    assert {k[0] for k in pick} == {"pack", "unpack", "repack"}
+    for k, code in pick.items():
         scales = _stores(code, "global_store_dword")
         assert scales, k
         assert not [s for s in scales if re.search(r"\bnt\b", s)], (k, scales)
