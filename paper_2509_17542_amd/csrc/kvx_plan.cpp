@@ -488,20 +488,27 @@ struct OneRequest {
 // from one shard; half a row where a dequantising lane writes each half by itself.
 // A piece of the cache ends with its page, which the next page of the launch
 // does not follow in memory.
+// Figures are of buffers that change from launch to launch.
 //  - Pieces that are not whole 64-byte sectors leave parts of a sector to
-//    another instruction: the L2 merges them (kStoreCached).  112-byte half
-//    rows 341 -> 270 us, 160-byte rows at 320 72 -> 58; written through they
-//    take 634 and 90.
-//    Pieces of 512 bytes on meet at few of their sectors and stream: 896-byte
-//    ones of a pack 107 us against 116 cached, in 300 MB of 2464-byte pages
-//    137 against 147.  The line is rough: two shards' 672- and 1568-byte pieces
-//    merged in 150 MB of cache take 69 and 59 us against 58 and 51 cached.
-//  - Broken sectors at the ends of short pages, whose other part belongs to
-//    another page, meet in the memory-side cache (256 MB) instead: kept in the
-//    L2 where the launch fits that, streamed where it does not, but for the
-//    shortest pages.  One-token pages of 160 bytes, streamed and cached: 137 and
-//    75 us in 200 MB, 279 and 261 in 400 MB; 176 bytes 235 and 166, 477 and
-//    477; 224 bytes 115 and 80, 239 and 247; 480 bytes 93 and 70, 192 and 216.
+//    another instruction: the L2 merges them (kStoreCached).  Two shards' 160-byte
+//    rows in 400 MB of cache 228 -> 159 us, 32-byte ones 344 -> 184; written
+//    through they take about twice as long.
+//    Long pieces meet at few of their sectors and stream: from 512 bytes on
+//    (streamed and cached: 672 bytes 68 and 71 us, 1568 bytes 59 and 65, 896 of a
+//    pack 107 and 118), in page-aligned packs of 16-bit rows from 384 on (400
+//    bytes 128.7 and 132.4, 416 bytes 145 and 150, 480 bytes 104 and 108.5; 224
+//    bytes 155 and 152).
+//  - The two half rows of a dequantising lane follow each other, so that their
+//    sectors meet without the L2's help but for the shortest: 112 bytes repacked
+//    into 400 MB 182 and 177 us, unpacked 139 and 130; but 144 bytes unpacked
+//    into 1.5 GB 464 and 521, 160 bytes repacked 567 and 584, 304 bytes 520 and
+//    560; and the unpack, with less arithmetic, into what the memory-side cache
+//    holds: 112 bytes, 150 MB, 52 and 57.
+//  - At the end of a short page the rest of a broken sector is another page's,
+//    which the L2 seldom holds at that time: only the shortest gain.  One-token
+//    pages of 80 bytes, 200 MB: 357 and 341 us, 96 bytes 180 and 157; 160 bytes
+//    67 and 67 in 100 MB, 176 bytes 235 and 243, 224 bytes 116 and 128, 480 bytes
+//    94 and 114.
 //  - Whole sectors stream past the caches.  Written through the L2 as well
 //    they reach memory in the order of the launch: packs 3% faster (14266
 //    tokens, 128 KB each: 580 -> 562 us; 1900 tokens 78.2 -> 75.4), 64 KB pages
@@ -534,8 +541,11 @@ int store_policy(const kvx_desc& d, const kvx::Shape& s, int mode, const kvx::KA
     const bool short_page = mode != kvx::kPack && run < piece;
     if (short_page) piece = run;
     if (piece % 64 || run % 64) {
-        const bool cached = short_page && large ? piece <= 160 : piece < 512;
-        return cached ? kvx::kStoreCached : kvx::kStoreStream;
+        int64_t below = 512;  // shorter pieces are left to the L2
+        if (short_page) below = 128;
+        else if (halves) below = mode == kvx::kUnpack && !large ? 0 : 128;
+        else if (mode == kvx::kPack && !flat_row_lanes && !is_fp8(d.dst_dtype)) below = 384;
+        return piece < below ? kvx::kStoreCached : kvx::kStoreStream;
     }
     if (flat_row_lanes || piece < (halves ? 192 : 128)) return kvx::kStoreStream;
     return mode == kvx::kPack || large ? kvx::kStoreThrough : kvx::kStoreStream;

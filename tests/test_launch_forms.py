@@ -47,7 +47,7 @@ def probe(tmp_path_factory):
 class Launch:
     """One plan in the probe; `launch(mode)` makes the call on made-up aligned
     addresses (nothing reads them) and returns its arguments."""
-    BT, STRIDE, SBT = 0x40000, 1 << 20, 0x50000
+    BT, STRIDE, SBT = 0x40000, 1 << 22, 0x50000
 
     def __init__(self, lib, desc):
         self.lib, self.desc, self.plan = lib, desc, ctypes.c_void_p()
@@ -80,54 +80,54 @@ class Launch:
         self.lib.kvx_plan_destroy(self.plan)
 
 
-def one_segment(heads, dim, page, wire=K.BF16, tokens=4096, cache=0):
-    """One shard to one rank: `heads` heads of `dim`, pages of `page` tokens."""
-    return K.make_desc(2, heads, dim, 1, 1, 0, K.BF16, wire, K.THD, page, 1 << 16, [tokens],
-                       cache_dtype=cache)
-
-
 # A flat launch's lanes follow one another across pages, but what they write
-# in one piece ends with the page: broken sectors of short pages are left to
-# the L2, whatever the rows of a wave add up to.
-SHORT_PAGES = [(1, 80, 1, K.BF16), (1, 112, 1, K.BF16), (3, 80, 1, K.BF16), (1, 16, 3, K.BF16),
-               (1, 80, 3, K.BF16), (1, 80, 1, K.E4M3FN), (1, 112, 1, K.E4M3FN),
-               (1, 80, 5, K.E4M3FN), (1, 16, 5, K.E4M3FN)]
+# in one piece ends with the page, whatever the rows of a wave add up to: only
+# broken sectors of the shortest pages are left to the L2.
+SHORT_PAGES = [(1, 40, 1, K.BF16, CACHED), (1, 48, 1, K.BF16, CACHED), (1, 16, 3, K.BF16, CACHED),
+               (1, 80, 1, K.E4M3FN, CACHED), (1, 112, 1, K.E4M3FN, CACHED),
+               (1, 16, 5, K.E4M3FN, CACHED), (1, 80, 1, K.BF16, STREAM),
+               (1, 112, 1, K.BF16, STREAM), (3, 80, 1, K.BF16, STREAM), (1, 80, 5, K.E4M3FN, STREAM),
+               (1, 80, 5, K.BF16, STREAM), (1, 128, 1, K.BF16, STREAM), (2, 96, 1, K.BF16, STREAM)]
 
 
 @pytest.mark.parametrize("mode", ["unpack", "repack"])
-@pytest.mark.parametrize("heads,dim,page,wire", SHORT_PAGES)
-def test_short_pages_of_broken_sectors_are_cached(probe, heads, dim, page, wire, mode):
-    run = heads * page * dim * (1 if wire == K.E4M3FN else 2)
-    assert run % 64 and run < 512
-    p = Launch(probe, one_segment(heads, dim, page, wire))
+@pytest.mark.parametrize("heads,dim,page,wire,store", SHORT_PAGES)
+def test_short_pages(probe, heads, dim, page, wire, store, mode):
+    for tokens in (4096, 2_000_000):            # below and above 256 MB of most
+        p = Launch(probe, K.make_desc(2, heads, dim, 1, 1, 0, K.BF16, wire, K.THD, page, 1 << 21,
+                                      [tokens]))
+        a = p.launch(mode)
+        p.close()
+        assert (a["form"], a["store"]) == (FLAT_CACHED if store == CACHED else FLAT, store)
+
+
+SMALL, LARGE = 4096, 300_000                    # tokens: 4 layers of 8 x 16 elements or more
+
+
+@pytest.mark.parametrize("dim,mode,tokens,store", [
+    (112, "repack", SMALL, CACHED), (112, "repack", LARGE, CACHED), (112, "unpack", SMALL, STREAM),
+    (112, "unpack", LARGE, CACHED), (144, "repack", SMALL, STREAM), (144, "repack", LARGE, STREAM),
+    (144, "unpack", SMALL, STREAM), (144, "unpack", LARGE, STREAM), (304, "repack", LARGE, STREAM)])
+def test_half_rows(probe, dim, mode, tokens, store):
+    """Broken half rows of a dequantising lane: left to the L2 below 128 bytes,
+    by the unpack into caches above 256 MB only."""
+    p = Launch(probe, K.make_desc(4, 8, dim, 1, 1, 0, K.BF16, K.E4M3FN, K.THD, 16, 1 << 20, [tokens],
+                                  cache_dtype=K.BF16))
+    assert (tokens * 4 * 2 * 8 * dim * 2 > 256 << 20) == (tokens == LARGE)
+    assert p.launch(mode)["store"] == store
+    p.close()
+
+
+@pytest.mark.parametrize("heads,dim,wire,mode,form,store", [
+    (2, 112, K.BF16, "pack", ALIGNED, CACHED),      # 224-byte pieces
+    (2, 208, K.BF16, "pack", ALIGNED, STREAM),      # 416
+    (2, 208, K.BF16, "repack", ALIGNED, CACHED),
+    (6, 80, K.BF16, "pack", FLAT_CACHED, CACHED),   # 480, rows packed chunk by chunk
+    (2, 464, K.E4M3FN, "pack", ALIGNED, CACHED),    # 464 bytes of codes
+    (6, 112, K.BF16, "repack", ALIGNED, STREAM)])   # 672
+def test_pieces_of_two_shards(probe, heads, dim, wire, mode, form, store):
+    p = Launch(probe, K.make_desc(2, heads, dim, 2, 1, 0, K.BF16, wire, K.THD, 16, 1 << 12, [4096]))
     a = p.launch(mode)
-    p.close()
-    assert (a["form"], a["store"]) == (FLAT_CACHED, CACHED)
-
-
-@pytest.mark.parametrize("heads,dim,page,store", [(1, 80, 1, CACHED), (1, 88, 1, STREAM),
-                                                  (1, 112, 1, STREAM), (3, 80, 1, STREAM)])
-def test_short_pages_above_the_memory_side_cache(probe, heads, dim, page, store):
-    """160, 176, 224 and 480 bytes, just above 256 MB of them."""
-    tokens = (256 << 20) // (2 * 2 * heads * dim * 2) + 1
-    p = Launch(probe, K.make_desc(2, heads, dim, 1, 1, 0, K.BF16, K.BF16, K.THD, page, 1 << 20,
-                                  [tokens]))
-    assert p.launch("repack")["store"] == store
-    p.close()
-    p = Launch(probe, K.make_desc(2, heads, dim, 1, 1, 0, K.BF16, K.BF16, K.THD, page, 1 << 20,
-                                  [tokens - 1]))
-    assert p.launch("repack")["store"] == CACHED
-    p.close()
-
-
-@pytest.mark.parametrize("heads,dim,page,wire,form,store", [
-    (1, 128, 1, K.BF16, FLAT, STREAM),          # 256-byte pages: whole sectors
-    (2, 96, 1, K.BF16, FLAT, STREAM),           # 384
-    (1, 80, 5, K.BF16, FLAT, STREAM),           # 800: broken, 512 bytes and more
-    (8, 128, 16, K.BF16, ALIGNED, STREAM)])     # 32 KB pages, a cache below 256 MB
-def test_other_pages_stream(probe, heads, dim, page, wire, form, store):
-    p = Launch(probe, one_segment(heads, dim, page, wire))
-    a = p.launch("repack")
     p.close()
     assert (a["form"], a["store"]) == (form, store)
 
