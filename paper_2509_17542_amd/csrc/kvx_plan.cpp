@@ -497,7 +497,8 @@ struct OneRequest {
 //    (streamed and cached: 672 bytes 68 and 71 us, 1568 bytes 59 and 65, 896 of a
 //    pack 107 and 118), in page-aligned packs of 16-bit rows from 384 on (400
 //    bytes 128.7 and 132.4, 416 bytes 145 and 150, 480 bytes 104 and 108.5; 224
-//    bytes 155 and 152).
+//    bytes 155 and 152).  Of unequal pieces the longer one decides (672 and 224
+//    bytes of a pack 27.5 and 29.6 us, of a repack 29.7 and 31.5).
 //  - The two half rows of a dequantising lane follow each other, so that their
 //    sectors meet without the L2's help but for the shortest: 112 bytes repacked
 //    into 400 MB 182 and 177 us, unpacked 139 and 130; but 144 bytes unpacked
@@ -527,11 +528,14 @@ int store_policy(const kvx_desc& d, const kvx::Shape& s, int mode, const kvx::KA
     else if (a.num_segs == 1)
         piece = flat_row_lanes == s.cpr ? 1024 : (64 >> s.lg_lpr) * piece;
     else {
-        const int64_t row = piece;
-        piece = a.seg0.n * row;
-        for (uint32_t j = 1; j < a.num_segs; ++j)  // the smallest, a broken sector first
-            if (k.seg[j].n * row % 64 || (piece % 64 == 0 && k.seg[j].n * row < piece))
-                piece = k.seg[j].n * row;
+        // the longest with a broken sector, else the shortest
+        int64_t broken = 0, whole = INT64_MAX;
+        for (uint32_t j = 0; j < a.num_segs; ++j) {
+            const int64_t bytes = k.seg[j].n * piece;
+            if (bytes % 64) broken = std::max(broken, bytes);
+            else whole = std::min(whole, bytes);
+        }
+        piece = broken ? broken : whole;
     }
     // the runs of rows that the pieces are cut from start in whole sectors too:
     // the pages of the cache, the tokens of the transfer tensor

@@ -132,6 +132,19 @@ def test_pieces_of_two_shards(probe, heads, dim, wire, mode, form, store):
     assert (a["form"], a["store"]) == (form, store)
 
 
+@pytest.mark.parametrize("mode", ["pack", "repack"])
+@pytest.mark.parametrize("dim", [112, 144, 208])
+def test_pieces_of_unequal_shards(probe, dim, mode):
+    """One head and three of another shard, and the mirror image: the longer
+    broken piece decides, in either order."""
+    for rank in (1, 3):
+        p = Launch(probe, K.make_desc(2, 20, dim, 4, 5, rank, K.BF16, K.BF16, K.THD, 16, 1 << 12,
+                                      [4096]))
+        a = p.launch(mode)
+        p.close()
+        assert a["segs"] == 2 and a["store"] == STREAM
+
+
 @pytest.mark.parametrize("mode", MODES)
 @pytest.mark.parametrize("name", list(FLAT_CASES))
 def test_flat_cases_are_flat(probe, name, mode):
